@@ -1,10 +1,24 @@
 // Maffettone-Minale droplet model (arXiv 2112.09972, Sec. 2 Eqs. 1, 2, 5) for
-// many trajectories at once: one thread per trajectory, FP64, classical RK4
-// with `substeps` steps per row of the velocity-gradient table, A(t) linear
-// between rows.  In the table's time unit the model reads
+// many trajectories at once: FP64, classical RK4 with `substeps` steps per row
+// of the velocity-gradient table, A(t) linear between rows.  In the table's time
+// unit the model reads
 //   dM/dt = f2(Ca) (S M + M S) + W M - M W - (f1/tau_d) (M - 3 det(M)/II_M I),
 // S, W the symmetric / antisymmetric parts of A, Ca = tau_d max|A_ij|,
-// II_M = (tr(M)^2 - M:M)/2, f1, f2 of Eq. 5; tau_d = eta_s R / sigma.
+// II_M = (tr(M)^2 - M:M)/2, f1, f2 of Eq. 5; tau_d = eta_s R / sigma.  With
+//   L = f2 S + W - (f1 / 2 tau_d) I
+// the same equation is dM/dt = L M + M L^T + 3 (f1/tau_d) det(M)/II_M I, and L
+// depends on the table alone.
+//
+// The trajectory is a serial chain of RK4 stages, so a launch of few trajectories
+// lasts as long as one of them: rows times the instructions a stage issues in the
+// wavefront that carries the chain.  Three things shorten it against one thread
+// doing all the work (64 trajectories of 20,001 rows: 46.8 ms, 2.3 us a row).
+//  - Folding f1 into L halves the products of a stage.
+//  - k_mm_quad: three wavefronts beside the chain's compute the matrices L of the coming
+//    substeps (table loads, Ca, f2) into LDS while the chain runs the present ones; one
+//    barrier a chunk.
+//  - A start from M = I keeps M symmetric, and in k_mm_quad three lanes of a quad share
+//    a trajectory.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -12,99 +26,271 @@
 
 namespace sclbm {
 
-struct Mat33 {
-    double m[9];
+struct MmArgs {
+    const double *A;   // [ntraj][nrows][9]
+    int64_t ntraj, nrows;
+    double tau_d, chi;
+    int substeps, record_every;
+    const double *M0;  // [ntraj][9] or null: the identity
+    double *out;       // [ntraj][nrec][9], nrec = 1 + (nrows - 1) / record_every, record r at time r * record_every
 };
 
-__device__ __forceinline__ void mm_rhs(const double *M, const double *A, double tau_d, double chi, double *out) {
-    double S[9], Wm[9];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            S[3 * i + j] = 0.5 * (A[3 * i + j] + A[3 * j + i]);
-            Wm[3 * i + j] = 0.5 * (A[3 * i + j] - A[3 * j + i]);
-        }
-    double gmax = 0.0;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) gmax = fmax(gmax, fabs(A[k]));
-    const double ca = tau_d * gmax;
-    const double f1 = 40.0 * (chi + 1.0) / ((3.0 + 2.0 * chi) * (16.0 + 19.0 * chi));
-    const double f2 = 5.0 / (3.0 + 2.0 * chi) + 3.0 * ca * ca / (2.0 + 6.0 * ca * ca);
-    const double tr = M[0] + M[4] + M[8];
-    double mm = 0.0;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) mm += M[k] * M[k];
-    const double II = 0.5 * (tr * tr - mm);
-    const double det = M[0] * (M[4] * M[8] - M[5] * M[7]) - M[1] * (M[3] * M[8] - M[5] * M[6]) +
-                       M[2] * (M[3] * M[7] - M[4] * M[6]);
-    const double c = 3.0 * det / II;
-    const double relax = f1 / tau_d;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            double sm = 0.0, ms = 0.0, wm = 0.0, mw = 0.0;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                sm += S[3 * i + k] * M[3 * k + j];
-                ms += M[3 * i + k] * S[3 * k + j];
-                wm += Wm[3 * i + k] * M[3 * k + j];
-                mw += M[3 * i + k] * Wm[3 * k + j];
-            }
-            out[3 * i + j] = f2 * (sm + ms) + wm - mw - relax * (M[3 * i + j] - (i == j ? c : 0.0));
-        }
+constexpr int MM_THREADS = 256;       // k_mm_quad: wavefront 0 carries the chains, 1 .. 3 prepare L
+constexpr int MM_QUAD_TRAJ = 16;      // trajectories of a workgroup, three lanes each
+constexpr int MM_LANE_TRAJ = 64;      // and one lane each
+
+// f1 / tau_d.  The same rounded value enters L and the det(M) / II_M term: where the two
+// differ by a rounding, det M (which the model conserves) drifts by that fraction of
+// f1 / tau_d every step (2.7e-14 against 1.5e-15 after 20,000 rows).
+__device__ __forceinline__ double mm_relax(const MmArgs &a) {
+    return 40.0 * (a.chi + 1.0) / ((3.0 + 2.0 * a.chi) * (16.0 + 19.0 * a.chi)) / a.tau_d;
 }
 
-// A: [ntraj][nrows][9]; M0 (optional): [ntraj][9]; out: [ntraj][nrec][9] with
-// nrec = 1 + (nrows - 1) / record_every, record r at time r * record_every.
-__global__ __launch_bounds__(64) void k_mm(const double *A, int64_t ntraj, int64_t nrows, double tau_d, double chi,
-                                           int substeps, int record_every, const double *M0, double *out) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= ntraj) return;
-    const double *At = A + t * nrows * 9;
-    const int64_t nrec = 1 + (nrows - 1) / record_every;
-    double *Ot = out + t * nrec * 9;
+// L at the fraction t of the way from row G0 to row G1.
+__device__ __forceinline__ void mm_matrix(const MmArgs &a, const double *G0, const double *G1, double t, double (&L)[9]) {
+    double G[9], gmax = 0.0;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        G[k] = G0[k] + (G1[k] - G0[k]) * t;
+        gmax = fmax(gmax, fabs(G[k]));
+    }
+    const double ca = a.tau_d * gmax;
+    const double f2 = 5.0 / (3.0 + 2.0 * a.chi) + 3.0 * ca * ca / (2.0 + 6.0 * ca * ca);
+    const double half_relax = 0.5 * mm_relax(a);
+    // f2 (G + G^T)/2 + (G - G^T)/2
+    const double cp = 0.5 * (f2 + 1.0), cm = 0.5 * (f2 - 1.0);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            L[3 * i + j] = i == j ? f2 * G[4 * i] - half_relax : cp * G[3 * i + j] + cm * G[3 * j + i];
+}
+
+// Value of v one (C = 0xC9) or two (0xD2) places on in the cyclic order of a quad's first three lanes.
+template <int CTRL>
+__device__ __forceinline__ double quad_rot(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_mov_dpp(int(uint32_t(u)), CTRL, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_mov_dpp(int(uint32_t(u >> 32)), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, uint64_t(lo) | (uint64_t(hi) << 32));
+}
+
+// Start from M = I: symmetric for all times.  Lane j of a quad holds a = M_jj and
+// b = M_j,j+1 (indices mod 3); the other four entries come from its neighbours.
+// A stage is 61 instructions (8 of them lane moves) and bound by the latency of the
+// dependent FP64 chain through det / II.  64 trajectories: 0.54 us a row (one lane a
+// trajectory, L in the chain: 1.07); 8192: 0.71 against 1.11.
+__global__ __launch_bounds__(MM_THREADS) void k_mm_quad(MmArgs a) {
+    constexpr int CH = 8;              // substeps of a chunk
+    constexpr int NS = 2 * CH + 1;     // half substeps whose L it needs
+    // per half substep, trajectory and lane j: L_jj, L_j,j+1, L_j,j+2, L_j+1,j, L_jj + L_j+1,j+1, L_j+1,j+2
+    __shared__ __attribute__((aligned(16))) double Ls[2][NS][MM_QUAD_TRAJ][3][6];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int64_t t0 = (int64_t)blockIdx.x * MM_QUAD_TRAJ;
+    const int64_t nsub = (a.nrows - 1) * a.substeps;
+    const int64_t nchunk = (nsub + CH - 1) / CH;
+    auto produce = [&](int64_t c, int first, int step) {
+        const int64_t n0 = c * CH / a.substeps;
+        const int s0 = int(c * CH % a.substeps);
+        for (int e = first; e < NS * MM_QUAD_TRAJ; e += step) {
+            const int tr = e / NS, m = e % NS;
+            const int64_t t = min(t0 + tr, a.ntraj - 1);
+            // row and fraction of the m-th half substep; a time beyond the table is taken at its end
+            const uint32_t hs = 2u * uint32_t(s0) + uint32_t(m), per = 2u * uint32_t(a.substeps);
+            int64_t n = n0 + hs / per;
+            uint32_t f = hs % per;
+            if (n >= a.nrows - 1) {
+                n = a.nrows - 2;
+                f = per;
+            }
+            const double *p = a.A + (t * a.nrows + n) * 9;
+            double L[9];
+            mm_matrix(a, p, p + 9, double(f) * (0.5 / double(a.substeps)), L);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const int j1 = (j + 1) % 3, j2 = (j + 2) % 3;
+                double *d = Ls[c & 1][m][tr][j];
+                d[0] = L[4 * j];
+                d[1] = L[3 * j + j1];
+                d[2] = L[3 * j + j2];
+                d[3] = L[3 * j1 + j];
+                d[4] = L[4 * j] + L[4 * j1];
+                d[5] = L[3 * j1 + j2];
+            }
+        }
+    };
+    if (nchunk > 0) produce(0, tid, MM_THREADS);
+    __syncthreads();
+    const int tr = lane >> 2, j = min(lane & 3, 2);
+    const int64_t t = t0 + tr;
+    const bool live = tid < 64 && (lane & 3) < 3 && t < a.ntraj;
+    double *Ot = a.out + t * (1 + (a.nrows - 1) / a.record_every) * 9;
+    const int j1 = (j + 1) % 3;
+    double ma = 1.0, mb = 0.0;
+    auto record = [&](int64_t r) {
+        if (!live) return;
+        Ot[r * 9 + 4 * j] = ma;
+        Ot[r * 9 + 3 * j + j1] = mb;
+        Ot[r * 9 + 3 * j1 + j] = mb;
+    };
+    record(0);
+    const double relax = mm_relax(a), h = 1.0 / a.substeps;
+    struct Coef {
+        double v[6];
+    };
+    auto fetch = [&](int buf, int m) {
+        Coef q;
+        const double2 *p = reinterpret_cast<const double2 *>(Ls[buf][m][tr][j]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const double2 v = p[k];
+            q.v[2 * k] = v.x;
+            q.v[2 * k + 1] = v.y;
+        }
+        return q;
+    };
+    auto rhs = [&](const Coef &q, double va, double vb, double &da, double &db) {
+        const double a1 = quad_rot<0xC9>(va), a2 = quad_rot<0xD2>(va);
+        const double b1 = quad_rot<0xC9>(vb), b2 = quad_rot<0xD2>(vb);
+        const double t01 = va * a1 - vb * vb, t12 = a1 * a2 - b1 * b1, t20 = a2 * va - b2 * b2;
+        const double II = t01 + t12 + t20;
+        const double det = va * t12 + b2 * (vb * b1 - a1 * b2) + vb * (b1 * b2 - a2 * vb);
+        const double p = q.v[0] * va + q.v[1] * vb + q.v[2] * b2;
+        db = q.v[4] * vb + q.v[3] * va + q.v[1] * a1 + q.v[2] * b1 + q.v[5] * b2;
+        da = (p + p) + relax * ((3.0 * det) / II);
+    };
+    int sub = 0, rec_in = a.record_every;
+    int64_t rec = 1;
+    for (int64_t c = 0; c < nchunk; ++c) {
+        if (tid < 64) {
+            const int buf = int(c & 1), len = int(min<int64_t>(CH, nsub - c * CH));
+            Coef La = fetch(buf, 0), Lm = fetch(buf, 1), Lb = fetch(buf, 2);
+            for (int s = 0; s < len; ++s) {
+                // the next substep's matrices (within the chunk's NS; unused after the last)
+                const Coef Lm2 = fetch(buf, min(2 * s + 3, NS - 1)), Lb2 = fetch(buf, min(2 * s + 4, NS - 1));
+                double ka, kb, sa, sb;
+                rhs(La, ma, mb, ka, kb);
+                sa = ka;
+                sb = kb;
+                rhs(Lm, ma + 0.5 * h * ka, mb + 0.5 * h * kb, ka, kb);
+                sa += 2.0 * ka;
+                sb += 2.0 * kb;
+                rhs(Lm, ma + 0.5 * h * ka, mb + 0.5 * h * kb, ka, kb);
+                sa += 2.0 * ka;
+                sb += 2.0 * kb;
+                rhs(Lb, ma + h * ka, mb + h * kb, ka, kb);
+                sa += ka;
+                sb += kb;
+                ma += (h / 6.0) * sa;
+                mb += (h / 6.0) * sb;
+                La = Lb;
+                Lm = Lm2;
+                Lb = Lb2;
+                if (++sub == a.substeps) {
+                    sub = 0;
+                    if (--rec_in == 0) {
+                        rec_in = a.record_every;
+                        record(rec++);
+                    }
+                }
+            }
+        } else if (c + 1 < nchunk) {
+            produce(c + 1, tid - 64, MM_THREADS - 64);
+        }
+        __syncthreads();
+    }
+}
+
+// Any M0 (M need not be symmetric), and launches of many trajectories: one lane a
+// trajectory, which computes L itself (twice a substep: the middle and the end; the end's
+// serves the next substep's start) and loads the next row while it integrates the
+// present one.  The issue rate binds once the device is full, so nothing is computed twice
+// here and no wavefront waits at a barrier.  65,536 trajectories: 1.43 us a row (one
+// thread with the unfolded equation 3.0; L prepared by other wavefronts 3.4).
+__global__ __launch_bounds__(MM_LANE_TRAJ) void k_mm_lane(MmArgs a) {
+    const int64_t t = (int64_t)blockIdx.x * MM_LANE_TRAJ + threadIdx.x;
+    if (t >= a.ntraj) return;
+    const double *At = a.A + t * a.nrows * 9;
+    double *Ot = a.out + t * (1 + (a.nrows - 1) / a.record_every) * 9;
     double M[9];
 #pragma unroll
-    for (int k = 0; k < 9; ++k) M[k] = M0 ? M0[t * 9 + k] : ((k % 4) == 0 ? 1.0 : 0.0);
+    for (int k = 0; k < 9; ++k) M[k] = a.M0 ? a.M0[t * 9 + k] : ((k % 4) == 0 ? 1.0 : 0.0);
+    auto record = [&](int64_t r) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) Ot[k] = M[k];
-    const double h = 1.0 / substeps;
-    for (int64_t n = 0; n + 1 < nrows; ++n) {
-        double A0[9], A1[9];
+        for (int k = 0; k < 9; ++k) Ot[r * 9 + k] = M[k];
+    };
+    record(0);
+    if (a.nrows < 2) return;
+    const double relax = mm_relax(a), h = 1.0 / a.substeps;
+    auto rhs = [&](const double (&L)[9], const double (&Y)[9], double (&out)[9]) {
+        const double tr = Y[0] + Y[4] + Y[8];
+        double mm = 0.0;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) mm += Y[k] * Y[k];
+        const double II = 0.5 * (tr * tr - mm);
+        const double det = Y[0] * (Y[4] * Y[8] - Y[5] * Y[7]) - Y[1] * (Y[3] * Y[8] - Y[5] * Y[6]) +
+                           Y[2] * (Y[3] * Y[7] - Y[4] * Y[6]);
+        const double c = (3.0 * det) / II;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                double s = 0.0;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    s += L[3 * i + k] * Y[3 * k + j];
+                    s += Y[3 * i + k] * L[3 * j + k];
+                }
+                out[3 * i + j] = i == j ? s + relax * c : s;
+            }
+    };
+    double G0[9], G1[9], G2[9], La[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        G0[k] = At[k];
+        G1[k] = At[9 + k];
+    }
+    mm_matrix(a, G0, G1, 0.0, La);
+    int rec_in = a.record_every;
+    int64_t rec = 1;
+    for (int64_t n = 0; n + 1 < a.nrows; ++n) {
+        const double *next = At + min(n + 2, a.nrows - 1) * 9;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) G2[k] = next[k];
+        for (int s = 0; s < a.substeps; ++s) {
+            double k[9], sum[9], Y[9], L[9];
+            rhs(La, M, k);
+            mm_matrix(a, G0, G1, (s + 0.5) * h, L);
+#pragma unroll
+            for (int e = 0; e < 9; ++e) {
+                sum[e] = k[e];
+                Y[e] = M[e] + 0.5 * h * k[e];
+            }
+            rhs(L, Y, k);
+#pragma unroll
+            for (int e = 0; e < 9; ++e) {
+                sum[e] += 2.0 * k[e];
+                Y[e] = M[e] + 0.5 * h * k[e];
+            }
+            rhs(L, Y, k);
+            mm_matrix(a, G0, G1, (s + 1) * h, La);
+#pragma unroll
+            for (int e = 0; e < 9; ++e) {
+                sum[e] += 2.0 * k[e];
+                Y[e] = M[e] + h * k[e];
+            }
+            rhs(La, Y, k);
+#pragma unroll
+            for (int e = 0; e < 9; ++e) M[e] += (h / 6.0) * (sum[e] + k[e]);
+        }
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
-            A0[k] = At[n * 9 + k];
-            A1[k] = At[(n + 1) * 9 + k];
+            G0[k] = G1[k];
+            G1[k] = G2[k];
         }
-        for (int s = 0; s < substeps; ++s) {
-            const double t0 = s * h;
-            double Aa[9], Am[9], Ab[9], k1[9], k2[9], k3[9], k4[9], Y[9];
-#pragma unroll
-            for (int k = 0; k < 9; ++k) {
-                const double d = A1[k] - A0[k];
-                Aa[k] = A0[k] + d * t0;
-                Am[k] = A0[k] + d * (t0 + 0.5 * h);
-                Ab[k] = A0[k] + d * (t0 + h);
-            }
-            mm_rhs(M, Aa, tau_d, chi, k1);
-#pragma unroll
-            for (int k = 0; k < 9; ++k) Y[k] = M[k] + 0.5 * h * k1[k];
-            mm_rhs(Y, Am, tau_d, chi, k2);
-#pragma unroll
-            for (int k = 0; k < 9; ++k) Y[k] = M[k] + 0.5 * h * k2[k];
-            mm_rhs(Y, Am, tau_d, chi, k3);
-#pragma unroll
-            for (int k = 0; k < 9; ++k) Y[k] = M[k] + h * k3[k];
-            mm_rhs(Y, Ab, tau_d, chi, k4);
-#pragma unroll
-            for (int k = 0; k < 9; ++k) M[k] += (h / 6.0) * (k1[k] + 2.0 * k2[k] + 2.0 * k3[k] + k4[k]);
-        }
-        if ((n + 1) % record_every == 0) {
-            const int64_t r = (n + 1) / record_every;
-#pragma unroll
-            for (int k = 0; k < 9; ++k) Ot[r * 9 + k] = M[k];
+        if (--rec_in == 0) {
+            rec_in = a.record_every;
+            record(rec++);
         }
     }
 }

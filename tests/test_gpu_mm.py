@@ -26,3 +26,26 @@ def test_mm_gpu_matches_reference():
     # deformations span a useful range
     Ds = [mm.deformation(M) for M in Mg[:, -1]]
     assert max(Ds) > 0.01
+
+
+@pytest.mark.parametrize("ntraj,nrows,substeps,every,start", [
+    (1, 1, 1, 1, "I"), (1, 2, 1, 1, "I"), (16, 9, 1, 3, "I"), (17, 10, 3, 1, "I"), (33, 8, 2, 7, "I"),
+    (8193, 6, 1, 2, "I"), (1, 1, 2, 1, "M0"), (1, 2, 1, 1, "M0"), (64, 4, 2, 1, "M0"), (65, 7, 3, 2, "M0")])
+def test_mm_chunks_and_starts(ntraj, nrows, substeps, every, start):
+    """Both kernels (start from I, any start) at the edges of their trajectory
+    groups (16 and 64) and substep chunks (8 and 2), an asymmetric start included,
+    against the FP64 reference.  Up to 27 RK4 steps of about 100 roundings of
+    1.1e-16 each on entries of order one: 3e-13 if they all added up."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2112_09972_amd as sc
+    rng = np.random.default_rng(ntraj * 100 + nrows)
+    A = 0.02 * rng.standard_normal((ntraj, nrows, 9))
+    M0 = None if start == "I" else np.eye(3).reshape(9) + 0.1 * rng.standard_normal((ntraj, 9))
+    got = sc.mm_integrate(A, 19.0, 1.3, substeps=substeps, record_every=every, M0=M0).cpu().numpy()
+    assert got.shape == (ntraj, 1 + (nrows - 1) // every, 3, 3)
+    for t in sorted({0, 15 % ntraj, 16 % ntraj, ntraj // 2, ntraj - 1}):
+        ref = mm.integrate(A[t].reshape(nrows, 3, 3), 19.0, 1.3, substeps=substeps, record_every=every,
+                           M0=None if M0 is None else M0[t].reshape(3, 3))
+        assert np.abs(got[t] - ref).max() <= 3e-13, (t, np.abs(got[t] - ref).max())
