@@ -130,65 +130,24 @@ __device__ __forceinline__ void node_moments(const typename Prec<P>::S *f, const
     }
 }
 
+// Densities of every node and, with j, the momentum j_A + j_B: one read of the populations
+// (bound by it: 54 us at 128^3 FP32, 6.5 TB/s, 63 us with the momentum written too).
 template <int P>
 __global__ __launch_bounds__(256) void k_density(const typename Prec<P>::S *f, const __half *ref, BoxGeom g,
-                                                 double *rho_a, double *rho_b) {
+                                                 double *rho_a, double *rho_b, double *j) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= g.nnode) return;
-    double rho[2], j[2][3];
-    node_moments<P>(f, ref, g, k, rho, j);
+    double rho[2], js[2][3];
+    node_moments<P>(f, ref, g, k, rho, js);
     rho_a[k] = rho[0];
     rho_b[k] = rho[1];
-}
-
-// Barycentric velocity with the half-force term; force from the FP64 density
-// arrays written by k_density (same neighbour rules as the step kernel).
-template <int P>
-__global__ __launch_bounds__(256) void k_velocity(const typename Prec<P>::S *f, const __half *ref, BoxGeom g,
-                                                  const double *rho_a, const double *rho_b, int ghost, double gab,
-                                                  double rb0, double rb1, double *u) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= g.nnode) return;
-    double rho[2], j[2][3];
-    node_moments<P>(f, ref, g, k, rho, j);
-    int x, y, z;
-    node_xyz(g, k, x, y, z);
-    const double *rf[2] = {rho_a, rho_b};
-    const double rbnd[2] = {rb0, rb1};
-    double Ft[3] = {0.0, 0.0, 0.0};
+    if (j) {
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const int o = 1 - s;
-        double sx = 0.0, sy = 0.0, sz = 0.0;
-#pragma unroll
-        for (int i = 1; i < Q; ++i) {
-            int nxp = x + cx_of(i), nyp = y + cy_of(i), nzp = z + cz_of(i);
-            double nb;
-            const bool inside = nxp >= 0 && nxp < g.nx && nyp >= 0 && nyp < g.ny && nzp >= 0 && nzp < g.nz;
-            if (inside || !ghost) {
-                nxp = (nxp + g.nx) % g.nx;
-                nyp = (nyp + g.ny) % g.ny;
-                nzp = (nzp + g.nz) % g.nz;
-                nb = rf[o][((int64_t)nzp * g.ny + nyp) * g.nx + nxp];
-            } else {
-                nb = rbnd[o];
-            }
-            const double wn = w_of<double>(i) * nb;
-            sx += cx_of(i) * wn;
-            sy += cy_of(i) * wn;
-            sz += cz_of(i) * wn;
-        }
-        const double pre = -gab * rho[s];
-        Ft[0] += pre * sx;
-        Ft[1] += pre * sy;
-        Ft[2] += pre * sz;
+        for (int c = 0; c < 3; ++c) j[c * g.nnode + k] = js[0][c] + js[1][c];
     }
-    const double rt = rho[0] + rho[1];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) u[c * g.nnode + k] = (j[0][c] + j[1][c] + 0.5 * Ft[c]) / rt;
 }
 
-template <int K>
+template <int K, int NT = NRED_THREADS>
 __device__ __forceinline__ void block_reduce_store(double (&v)[K], double *out /* K values */) {
     // wavefront butterfly, fixed order
 #pragma unroll
@@ -196,7 +155,7 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[K], double *out /
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) v[c] += __shfl_down(v[c], off, 64);
     }
-    __shared__ double part[NRED_THREADS / 64][K];
+    __shared__ double part[NT / 64][K];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (lane == 0)
 #pragma unroll
@@ -204,9 +163,167 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[K], double *out /
     __syncthreads();
     if (threadIdx.x < K) {
         double acc = 0.0;
-        for (int w = 0; w < NRED_THREADS / 64; ++w) acc += part[w][threadIdx.x];
+        for (int w = 0; w < NT / 64; ++w) acc += part[w][threadIdx.x];
         out[threadIdx.x] = acc;
     }
+}
+
+// Barycentric velocity with the half-force term from the densities and momenta written by
+// k_density (same neighbour rules as the step kernel): in place, u in the momentum's array,
+// or with E0 the sums of |u - A d|^2 and |A d|^2 (Sec. 4 Eq. 16) per workgroup instead.
+//
+// The momentum costs 48 B a node of traffic where summing the populations again would read
+// 152 (FP32).  Tiles of 64 x 8 nodes march along z with one plane of densities, ring
+// included, in LDS (two buffers, one barrier a plane); the next plane's loads are under way
+// meanwhile.  A plane enters the stencil of its own nodes and, through three sums per
+// node, that of the planes on either side, so each is read from LDS once: 18 reads a node.
+// 36 us at 128^3 and 202 us at 256^3 (5.3 TB/s); gathering the 36 neighbours from global
+// memory instead 69 and 529 us, and summing the populations again as well 187 us (128^3
+// FP32) and 1322 us (256^3 FP16).
+// The items (x tile, y tile, z-chunk) of a workgroup are consecutive, and the workgroups of
+// one XCD next to one another, so that rings and chunk ends hit in its L2.
+constexpr int VEL_TX = 64, VEL_TY = 8, VEL_THREADS = VEL_TX * VEL_TY;
+constexpr int VEL_BLOCKS = 2048;  // most workgroups of a launch
+constexpr int VEL_RING = 2 * (VEL_TX + 2) + 2 * VEL_TY;
+template <bool E0>
+__global__ __launch_bounds__(VEL_THREADS) void k_velocity(BoxGeom g, const double *rho_a, const double *rho_b, int ghost,
+                                                          double gab, double rb0, double rb1, double *u, int zchunk,
+                                                          Mat3 A, double *partial) {
+    __shared__ double ld[2][2][VEL_TY + 2][VEL_TX + 2];
+    const int ntx = (g.nx + VEL_TX - 1) / VEL_TX, nty = (g.ny + VEL_TY - 1) / VEL_TY;
+    const uint32_t nitem = uint32_t(ntx) * uint32_t(nty) * uint32_t((g.nz + zchunk - 1) / zchunk);
+    const uint32_t q8 = gridDim.x / 8, r8 = gridDim.x % 8, xcd = blockIdx.x % 8, k8 = blockIdx.x / 8;
+    const uint32_t blk = xcd < r8 ? xcd * (q8 + 1) + k8 : r8 * (q8 + 1) + (xcd - r8) * q8 + k8;
+    const uint32_t first = uint32_t(uint64_t(blk) * nitem / gridDim.x);
+    const uint32_t last = uint32_t(uint64_t(blk + 1) * nitem / gridDim.x);
+    const uint32_t nxy = uint32_t(g.nx) * uint32_t(g.ny);
+    const int tid = threadIdx.x, lx = tid & 63, ly = tid >> 6;
+    const double rbnd[2] = {rb0, rb1};
+    double v[2] = {0.0, 0.0};
+    for (uint32_t item = first; item < last; ++item) {
+        const int x0 = int(item % uint32_t(ntx)) * VEL_TX, y0 = int(item / uint32_t(ntx) % uint32_t(nty)) * VEL_TY;
+        const int zs = int(item / uint32_t(ntx) / uint32_t(nty)) * zchunk, ze = min(zs + zchunk, g.nz);
+        const int x = x0 + lx, y = y0 + ly;
+        const bool valid = x < g.nx && y < g.ny;
+        // the ring node of this thread: rows y0 - 1 and y0 + VEL_TY, then columns x0 - 1 and x0 + VEL_TX
+        const bool ring_on = tid < VEL_RING;
+        int rx, ry;
+        if (tid < 2 * (VEL_TX + 2)) {
+            ry = tid < VEL_TX + 2 ? 0 : VEL_TY + 1;
+            rx = tid < VEL_TX + 2 ? tid : tid - (VEL_TX + 2);
+        } else {
+            const int r = tid - 2 * (VEL_TX + 2);
+            rx = r < VEL_TY ? 0 : VEL_TX + 1;
+            ry = 1 + (r < VEL_TY ? r : r - VEL_TY);
+        }
+        // offset of a (x, y) in its plane after the wrap; false where it is a ghost or lies beyond
+        // the one node past the box that a valid node's stencil reaches
+        auto place = [&](int px, int py, uint32_t &off) {
+            const bool in = px >= 0 && px < g.nx && py >= 0 && py < g.ny;
+            const bool reach = px <= g.nx && py <= g.ny;
+            if (!ghost) {
+                px = px < 0 ? px + g.nx : (px >= g.nx ? px - g.nx : px);
+                py = py < 0 ? py + g.ny : (py >= g.ny ? py - g.ny : py);
+            }
+            off = uint32_t(py) * uint32_t(g.nx) + uint32_t(px);
+            return ghost ? in : reach;
+        };
+        uint32_t own_off, ring_off;
+        const bool own_in = place(x, y, own_off);
+        const bool ring_in = ring_on && place(x0 - 1 + rx, y0 - 1 + ry, ring_off);
+        double own[2], ring[2];
+        auto load = [&](int z) {
+            const bool zin = z >= 0 && z < g.nz;
+            const int zz = zin ? z : (z < 0 ? z + g.nz : z - g.nz);
+            const bool live = zin || !ghost;
+            const uint32_t base = uint32_t(zz) * nxy;
+            own[0] = rbnd[0];
+            own[1] = rbnd[1];
+            if (own_in && live) {
+                own[0] = rho_a[base + own_off];
+                own[1] = rho_b[base + own_off];
+            }
+            ring[0] = rbnd[0];
+            ring[1] = rbnd[1];
+            if (ring_in && live) {
+                ring[0] = rho_a[base + ring_off];
+                ring[1] = rho_b[base + ring_off];
+            }
+        };
+        // per component: stencil sums of the node's own plane (sx, sy) and the terms (c, dx, dy)
+        // it adds to the planes beside it: c to sz, with the sign of the step, dx and dy to sx and sy
+        struct Plane {
+            double sx[2], sy[2], c[2], dx[2], dy[2], rho[2];
+        };
+        Plane p0{}, p1{};  // planes z - 2 and z - 1
+        load(zs - 1);
+        for (int z = zs - 1; z <= ze; ++z) {
+            double(*const pl)[VEL_TY + 2][VEL_TX + 2] = ld[(z - zs + 1) & 1];
+            pl[0][ly + 1][lx + 1] = own[0];
+            pl[1][ly + 1][lx + 1] = own[1];
+            if (ring_on) {
+                pl[0][ry][rx] = ring[0];
+                pl[1][ry][rx] = ring[1];
+            }
+            __syncthreads();
+            Plane p2;
+            p2.rho[0] = own[0];
+            p2.rho[1] = own[1];
+            if (z < ze) load(z + 1);
+            const int zc = z - 1;
+            const uint32_t k = uint32_t(zc) * nxy + own_off;
+            const bool emit = zc >= zs && valid;
+            double jm[3] = {0.0, 0.0, 0.0};
+            if (emit) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) jm[c] = u[c * g.nnode + k];
+            }
+            constexpr double w1 = 1.0 / 18.0, w2 = 1.0 / 36.0;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                auto at = [&](int cx, int cy) { return pl[s][ly + 1 + cy][lx + 1 + cx]; };
+                const double xp = at(1, 0), xm = at(-1, 0), yp = at(0, 1), ym = at(0, -1);
+                const double pp = at(1, 1), mm = at(-1, -1), pm = at(1, -1), mp = at(-1, 1);
+                p2.sx[s] = w1 * (xp - xm) + w2 * ((pp - mm) + (pm - mp));
+                p2.sy[s] = w1 * (yp - ym) + w2 * ((pp - mm) - (pm - mp));
+                p2.c[s] = w1 * p2.rho[s] + w2 * ((xp + xm) + (yp + ym));
+                p2.dx[s] = w2 * (xp - xm);
+                p2.dy[s] = w2 * (yp - ym);
+            }
+            if (emit) {
+                double F[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const int o = 1 - s;
+                    const double pre = -gab * p1.rho[s];
+                    F[0] += pre * (p1.sx[o] + (p0.dx[o] + p2.dx[o]));
+                    F[1] += pre * (p1.sy[o] + (p0.dy[o] + p2.dy[o]));
+                    F[2] += pre * (p2.c[o] - p0.c[o]);
+                }
+                const double rt = p1.rho[0] + p1.rho[1];
+                double vel[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) vel[c] = (jm[c] + 0.5 * F[c]) / rt;
+                if constexpr (E0) {
+                    const double dx = x - g.xc[0], dy = y - g.xc[1], dz = zc - g.xc[2];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const double lin = A.a[3 * c] * dx + A.a[3 * c + 1] * dy + A.a[3 * c + 2] * dz;
+                        const double e = vel[c] - lin;
+                        v[0] += e * e;
+                        v[1] += lin * lin;
+                    }
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) u[c * g.nnode + k] = vel[c];
+                }
+            }
+            p0 = p1;
+            p1 = p2;
+        }
+        __syncthreads();  // the next item writes the buffer the last plane was read from
+    }
+    if constexpr (E0) block_reduce_store<2, VEL_THREADS>(v, partial + (int64_t)blk * 2);
 }
 
 // Per-workgroup partials of: mass A, mass B, momentum (3), indicator moments
@@ -335,24 +452,6 @@ __global__ __launch_bounds__(NRED_THREADS) void k_stats(const typename Prec<P>::
         }
     }
     block_reduce_store<NSTAT>(v, partial + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * NSTAT);
-}
-
-// Partials of sum |u - A d|^2 and sum |A d|^2 (Sec. 4 Eq. 16).
-__global__ __launch_bounds__(NRED_THREADS) void k_e0(const double *u, BoxGeom g, Mat3 A, double *partial) {
-    double v[2] = {0.0, 0.0};
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < g.nnode; k += stride) {
-        int x, y, z;
-        node_xyz(g, k, x, y, z);
-        const double dx = x - g.xc[0], dy = y - g.xc[1], dz = z - g.xc[2];
-        const double vx = A.a[0] * dx + A.a[1] * dy + A.a[2] * dz;
-        const double vy = A.a[3] * dx + A.a[4] * dy + A.a[5] * dz;
-        const double vz = A.a[6] * dx + A.a[7] * dy + A.a[8] * dz;
-        const double ex = u[k] - vx, ey = u[g.nnode + k] - vy, ez = u[2 * g.nnode + k] - vz;
-        v[0] += ex * ex + ey * ey + ez * ez;
-        v[1] += vx * vx + vy * vy + vz * vz;
-    }
-    block_reduce_store<2>(v, partial + (int64_t)blockIdx.x * 2);
 }
 
 // Fixed-order sum of nblk partials of K values each; workgroup b handles the

@@ -451,21 +451,43 @@ sclbm_status launch_drop_mass(sclbm_ctx *c, int32_t b0, int32_t nb) {
     return SCLBM_OK;
 }
 
-sclbm_status fields_into(sclbm_ctx *c, int32_t box, double *ra, double *rb, double *u) {
+// Densities of a box and, with j, its momenta j_A + j_B [3][N].
+sclbm_status launch_density(sclbm_ctx *c, int32_t box, double *ra, double *rb, double *j) {
     hipError_t e = by_prec(c->cfg.prec, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
         using S = typename Prec<P>::S;
         const S *f = reinterpret_cast<const S *>(c->fbuf(c->par)) + size_t(box) * 2 * Q * size_t(c->N);
         hipLaunchKernelGGL((k_density<P>), dim3(grid1d(c->N, 256)), dim3(256), 0, c->stream, f,
-                           c->box_ref(c->par, box), c->geom, ra, rb);
-        hipError_t e1 = hipGetLastError();
-        if (e1 != hipSuccess || !u) return e1;
-        hipLaunchKernelGGL((k_velocity<P>), dim3(grid1d(c->N, 256)), dim3(256), 0, c->stream, f,
-                           c->box_ref(c->par, box), c->geom, ra, rb, int(c->cfg.bc == SCLBM_BC_GHOST), c->cfg.g_ab,
-                           c->cfg.rho_b[0], c->cfg.rho_b[1], u);
+                           c->box_ref(c->par, box), c->geom, ra, rb, j);
         return hipGetLastError();
     });
-    if (e != hipSuccess) return fail(SCLBM_EHIP, "fields kernels: %s", hipGetErrorString(e));
+    if (e != hipSuccess) return fail(SCLBM_EHIP, "density kernel: %s", hipGetErrorString(e));
+    return SCLBM_OK;
+}
+
+// Launch of k_velocity: z-chunks long enough that the two planes read beyond each cost
+// little, but about four workgroups per CU where the box has the planes for it (at least 4 a
+// chunk); at most VEL_BLOCKS workgroups, so that their E0 partials fit the workspace's (at
+// least NRED_BLOCKS x NSTAT values).
+static_assert(VEL_BLOCKS * 2 <= NRED_BLOCKS * NSTAT, "E0 partials");
+void velocity_launch(const sclbm_ctx *c, int &zchunk, int &blocks) {
+    const int64_t tiles = int64_t((c->cfg.nx + VEL_TX - 1) / VEL_TX) * ((c->cfg.ny + VEL_TY - 1) / VEL_TY);
+    const int64_t want = std::min<int64_t>((1024 + tiles - 1) / tiles, std::max(1, c->cfg.nz / 4));
+    zchunk = int((c->cfg.nz + want - 1) / want);
+    blocks = int(std::min<int64_t>(tiles * ((c->cfg.nz + zchunk - 1) / zchunk), VEL_BLOCKS));
+}
+
+// Velocity of a box from ra, rb and the momenta in u (overwritten), or with E0 the error
+// sums against the flow A in c->partial().
+template <bool E0>
+sclbm_status launch_velocity(sclbm_ctx *c, const double *ra, const double *rb, double *u, const Mat3 &A,
+                             int *nblocks = nullptr) {
+    int zchunk, blocks;
+    velocity_launch(c, zchunk, blocks);
+    k_velocity<E0><<<blocks, VEL_THREADS, 0, c->stream>>>(c->geom, ra, rb, int(c->cfg.bc == SCLBM_BC_GHOST), c->cfg.g_ab,
+                                                         c->cfg.rho_b[0], c->cfg.rho_b[1], u, zchunk, A, c->partial());
+    HIP_LAUNCHED();
+    if (nblocks) *nblocks = blocks;
     return SCLBM_OK;
 }
 
@@ -890,7 +912,8 @@ sclbm_status sclbm_fields(sclbm_ctx *c, int32_t box, double *rho_a, double *rho_
     if (st) return st;
     if ((st = check_box(c, box, false))) return st;
     if (!rho_a || !rho_b) return fail(SCLBM_EINVAL, "rho_a and rho_b must not be NULL");
-    return fields_into(c, box, rho_a, rho_b, u);
+    if ((st = launch_density(c, box, rho_a, rho_b, u)) || !u) return st;
+    return launch_velocity<false>(c, rho_a, rho_b, u, Mat3{});
 }
 
 sclbm_status sclbm_totals(sclbm_ctx *c, int32_t box, double mass[2], double momentum[3]) {
@@ -1080,14 +1103,13 @@ sclbm_status sclbm_velocity_error(sclbm_ctx *c, int32_t box, const double A[9], 
     if ((st = check_box(c, box, false))) return st;
     if (!A || !e0) return fail(SCLBM_EINVAL, "null argument");
     double *d = c->diag();
-    if ((st = fields_into(c, box, d, d + c->N, d + 2 * c->N))) return st;
+    if ((st = launch_density(c, box, d, d + c->N, d + 2 * c->N))) return st;
     Mat3 m;
     for (int k = 0; k < 9; ++k) m.a[k] = A[k];
-    hipLaunchKernelGGL(k_e0, dim3(NRED_BLOCKS), dim3(NRED_THREADS), 0, c->stream, d + 2 * c->N, c->geom, m,
-                       c->partial());
-    HIP_LAUNCHED();
+    int blocks = 0;
+    if ((st = launch_velocity<true>(c, d, d + c->N, d + 2 * c->N, m, &blocks))) return st;
     double r[2];
-    if ((st = reduce_final<2>(c, NRED_BLOCKS, r))) return st;
+    if ((st = reduce_final<2>(c, blocks, r))) return st;
     if (!(r[1] > 0.0)) return fail(SCLBM_EINVAL, "the imposed flow is zero on this box");
     *e0 = std::sqrt(r[0]) / std::sqrt(r[1]);
     return SCLBM_OK;

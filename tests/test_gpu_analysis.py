@@ -116,3 +116,33 @@ def test_analysis_errors(sc):
         lat.reinject([1.0], box=3)
     with pytest.raises(sc.SclbmError):
         sc.sclbm_deformation_lbm(0.0, 1.0)
+
+
+@pytest.mark.parametrize("bc", ["ghost", "periodic"])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16dev"])
+@pytest.mark.parametrize("nxyz", [(3, 3, 3), (64, 4, 5), (65, 5, 4), (129, 3, 7), (20, 37, 41)])
+def test_fields_and_velocity_error_on_ragged_boxes(sc, nxyz, prec, bc):
+    """Densities, velocity and E0 of random fields at the edges of the velocity
+    pass's 64 x 4 tiles, both boundaries.  FP64: up to 40 roundings of sums of order
+    one.  FP32 and FP16 deviations: an equilibrium population carries a relative
+    error of 2^-24 (FP16: 2^-11 of its deviation, up to 0.5 of it here), 2 x 19 of
+    them add up to at most that share of rho, and of the velocity's w c sums."""
+    nx, ny, nz = nxyz
+    rng = np.random.default_rng(nx * 7 + ny)
+    ra = rng.uniform(0.2, 1.0, (nz, ny, nx))
+    rb = rng.uniform(0.2, 1.0, (nz, ny, nx))
+    u = 0.05 * rng.standard_normal((3, nz, ny, nx))
+    A = np.array([[1e-3, 2e-3, 0], [0, -4e-3, 1e-3], [3e-3, 0, 3e-3]])
+    lat = sc.Lattice(nx, ny, nz, bc=bc, prec=prec, table_len=1, g_ab=wl.G_AB, rho_b=(0.05, 1.0))
+    o = oracle.Oracle(nx, ny, nz, periodic=bc == "periodic", g=wl.G_AB, rho_b=(0.05, 1.0))
+    lat.init_fields(ra, rb, u)
+    o.init_fields(ra, rb, u)
+    got = [t.cpu().numpy() for t in lat.fields()]
+    ref = o.fields()
+    tol = {"f64": 1e-14, "f32": 2.0 ** -22, "f16dev": 2.0 ** -10}[prec]
+    for g, r in zip(got, ref):
+        assert np.abs(g - r).max() <= tol * max(1.0, np.abs(r).max())
+    dens = [t.cpu().numpy() for t in lat.fields(velocity=False)]
+    assert np.array_equal(dens[0], got[0]) and np.array_equal(dens[1], got[1])
+    # E0 of the velocities above, from the same formula on the host
+    assert lat.velocity_error(A.reshape(9)) == pytest.approx(oracle.velocity_error(got[2], A.reshape(9), o.xc), rel=1e-12)
