@@ -7,9 +7,6 @@
 
 namespace sclbm {
 
-constexpr int SURF_T = 16;               // cells per tile edge (x and y); one thread per cell
-constexpr int SURF_P = SURF_T + 1;       // nodes per tile edge
-
 // Zero set of phi (linear inside the tetrahedron with corners p[0..3], values s[0..3]):
 // adds its area and the volume of {phi > 0}.  The volume uses the edge fractions of the
 // cut (barycentric closed forms); the tetrahedron's volume is 1/6 (one sixth of a cell).
@@ -72,77 +69,100 @@ __device__ __forceinline__ void tet_cut(const double (&p)[4][3], const double (&
     vol += V6 * (al * be + al * de * (1.0 - be) + (1.0 - al) * ga * de);
 }
 
-// Area of {phi = 0} and volume of {phi > 0}, phi = rho_A - rho_B, over the cells of each
-// box.  Grid (tile blocks, boxes); a block takes tiles of 16 x 16 cells, marching in z
-// with two planes of phi in LDS (each node's populations read about 1.13 times).
+// phi = rho_A - rho_B of every node, phi[box][node]; grid (blocks of 256 nodes, boxes).
 template <int P>
-__global__ __launch_bounds__(NRED_THREADS) void k_surface(const typename Prec<P>::S *f, const __half *ref, BoxGeom g,
-                                                          int b0, int ntx, int ntiles, double *partial) {
-    static_assert(NRED_THREADS == SURF_T * SURF_T, "one thread per cell of a tile");
-    const int box = b0 + blockIdx.y;
+__global__ __launch_bounds__(NRED_THREADS) void k_phi(const typename Prec<P>::S *f, const __half *ref, BoxGeom g,
+                                                      double *phi) {
+    const int box = blockIdx.y;
+    const int64_t k = (int64_t)blockIdx.x * NRED_THREADS + threadIdx.x;
+    if (k >= g.nnode) return;
     f += (int64_t)box * 2 * Q * g.nnode;
     if (Prec<P>::DEV) ref += (int64_t)box * 2 * g.nnode;
-    __shared__ double ph[2][SURF_P * SURF_P];
-    const int ci = threadIdx.x % SURF_T, cj = threadIdx.x / SURF_T;
+    double rho[2], j[2][3];
+    node_moments<P>(f, ref, g, k, rho, j);
+    phi[(int64_t)box * g.nnode + k] = rho[0] - rho[1];
+}
+
+// Area of {phi = 0} and volume of {phi > 0} over the cells of each box; grid (blocks, boxes),
+// cell (x, y, z) to (x + 1, y + 1, z + 1) with its lowest corner's thread.
+//
+// The populations are read once, node by node, by k_phi (bound by that read: 53 us at 128^3
+// FP32), and the cells take phi from an array that fits the caches: 8 B a node written and read
+// against 152 of populations.  One kernel that marched 16 x 16 cells along z and summed the
+// populations of its 17 x 17 nodes on the way had one workgroup per column of cells (64 at
+// 128^3, a quarter of the CUs) and two barriers a plane: 1316 us.
+// Thread t takes nodes t, t + stride, ... and carries (x, y, z) on, as k_stats does.  Few of
+// the 64 cells a wavefront looks at are cut by the interface, so it only notes them, in a list
+// of its own in lane order, and then gives each of its lanes one tetrahedron of one noted
+// cell at a time (cutting the six of a cell in the cell's own lane left most lanes idle:
+// 62 against 22 us at 128^3).  The sums' order is fixed.
+constexpr int SURF_LIST = 256;  // cells a wavefront notes before it cuts them
+__global__ __launch_bounds__(NRED_THREADS) void k_surface(const double *phi, BoxGeom g, double *partial) {
+    __shared__ uint32_t list[NRED_THREADS / 64][SURF_LIST];
+    phi += (int64_t)blockIdx.y * g.nnode;
+    const int lane = threadIdx.x & 63;
+    uint32_t *const mine = list[threadIdx.x >> 6];
+    const uint32_t nn = uint32_t(g.nnode), nx = uint32_t(g.nx), ny = uint32_t(g.ny), nz = uint32_t(g.nz);
+    const uint32_t nxy = nx * ny;
+    const uint32_t stride = gridDim.x * NRED_THREADS;
+    uint32_t k = blockIdx.x * NRED_THREADS + threadIdx.x;
+    uint32_t x = k % nx, y = (k / nx) % ny, z = k / nx / ny;
+    const uint32_t sx = stride % nx, sy = (stride / nx) % ny, sz = stride / nx / ny;
     double v[2] = {0.0, 0.0};
-    // the six tetrahedra of a cell: corner 0, then one unit step along each axis in turn
-    const int perm[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
-    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int x0 = (tile % ntx) * SURF_T, y0 = (tile / ntx) * SURF_T;
-        for (int z = 0; z < g.nz; ++z) {
-            double *dst = ph[z & 1];
-            for (int n = threadIdx.x; n < SURF_P * SURF_P; n += NRED_THREADS) {
-                const int x = x0 + n % SURF_P, y = y0 + n / SURF_P;
-                double val = 0.0;
-                if (x < g.nx && y < g.ny) {
-                    double rho[2], j[2][3];
-                    node_moments<P>(f, ref, g, ((int64_t)z * g.ny + y) * g.nx + x, rho, j);
-                    val = rho[0] - rho[1];
-                }
-                dst[n] = val;
+    int count = 0;  // noted cells, the same in every lane
+    auto cut = [&]() {
+        __builtin_amdgcn_wave_barrier();  // the list's writes stand before its reads (one wavefront, in order)
+        for (int e = lane; e < 6 * count; e += 64) {
+            const uint32_t c = mine[e / 6];
+            const int t = e % 6;
+            // tetrahedron t: from the cell's lowest corner one step along each axis, in the t-th
+            // order of (x, y, z); coordinates relative to that corner (the sums do not change)
+            const int a0 = t >> 1, a1 = (t & 1) ? (a0 == 2 ? 1 : 2) : (a0 == 0 ? 1 : 0);
+            const uint32_t off0 = a0 == 0 ? 1u : (a0 == 1 ? nx : nxy), off1 = a1 == 0 ? 1u : (a1 == 1 ? nx : nxy);
+            double pp[4][3], ss[4];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                pp[0][d] = 0.0;
+                pp[1][d] = d == a0 ? 1.0 : 0.0;
+                pp[2][d] = d == a0 || d == a1 ? 1.0 : 0.0;
+                pp[3][d] = 1.0;
             }
-            __syncthreads();
-            const int x = x0 + ci, y = y0 + cj;
-            if (z > 0 && x + 1 < g.nx && y + 1 < g.ny) {
-                const double *lo = ph[(z - 1) & 1], *hi = ph[z & 1];
-                double c8[2][2][2];  // [dz][dy][dx]
-#pragma unroll
-                for (int dy = 0; dy < 2; ++dy)
-#pragma unroll
-                    for (int dx = 0; dx < 2; ++dx) {
-                        c8[0][dy][dx] = lo[(cj + dy) * SURF_P + ci + dx];
-                        c8[1][dy][dx] = hi[(cj + dy) * SURF_P + ci + dx];
-                    }
-                bool any_pos = false, any_neg = false;
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const double s = c8[q >> 2][(q >> 1) & 1][q & 1];
-                    any_pos |= s > 0.0;
-                    any_neg |= !(s > 0.0);
-                }
-                if (any_pos && !any_neg) {
-                    v[1] += 1.0;                 // a cell wholly inside
-                } else if (any_pos) {
-                    // coordinates relative to the cell's corner (the sums are translation invariant)
-#pragma unroll
-                    for (int t = 0; t < 6; ++t) {
-                        double pp[4][3], ss[4];
-                        int o[3] = {0, 0, 0};
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            if (k > 0) o[perm[t][k - 1]] = 1;
-                            pp[k][0] = o[0];
-                            pp[k][1] = o[1];
-                            pp[k][2] = o[2];
-                            ss[k] = c8[o[2]][o[1]][o[0]];
-                        }
-                        tet_cut(pp, ss, v[0], v[1]);
-                    }
-                }
-            }
-            __syncthreads();
+            ss[0] = phi[c];
+            ss[1] = phi[c + off0];
+            ss[2] = phi[c + off0 + off1];
+            ss[3] = phi[c + 1u + nx + nxy];
+            tet_cut(pp, ss, v[0], v[1]);
         }
+        count = 0;
+    };
+    // every lane of a wavefront stays in the loop until its last one is done
+    while (__any(k < nn)) {
+        bool noted = false;
+        if (k < nn && x + 1 < nx && y + 1 < ny && z + 1 < nz) {
+            bool any_pos = false, any_neg = false;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const double s = phi[k + uint32_t(q >> 2) * nxy + uint32_t((q >> 1) & 1) * nx + uint32_t(q & 1)];
+                any_pos |= s > 0.0;
+                any_neg |= !(s > 0.0);
+            }
+            noted = any_pos && any_neg;
+            if (any_pos && !any_neg) v[1] += 1.0;  // a cell wholly inside
+        }
+        const uint64_t who = __ballot(noted);
+        if (noted) mine[count + __popcll(who & ((1ull << lane) - 1ull))] = k;
+        count += __popcll(who);
+        if (count > SURF_LIST - 64) cut();
+        k = k < nn ? k + stride : k;
+        x += sx;
+        const uint32_t carry_x = x >= nx ? 1u : 0u;
+        x -= carry_x * nx;
+        y += sy + carry_x;
+        const uint32_t carry_y = y >= ny ? 1u : 0u;
+        y -= carry_y * ny;
+        z += sz + carry_y;
     }
+    cut();
     block_reduce_store<2>(v, partial + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 2);
 }
 

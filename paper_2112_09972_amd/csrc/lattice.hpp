@@ -181,14 +181,16 @@ template <>
 struct Prec<SCLBM_F32D> : PrecF32<double> {};
 // The deviation formats as the auxiliary kernels (initialisation, fields,
 // moments) read and write them, one population at a time; the step kernel
-// (k_step_dev) has its own arithmetic on the stored deviations.
+// (k_step_dev) has its own arithmetic on the stored deviations.  The decode is an
+// explicit multiply-add: left to contraction, a kernel may round w_i rho_ref once or
+// not at all, and two kernels then see densities of a node that differ by 1e-8.
 template <>
 struct Prec<SCLBM_F16DEV> {
     static constexpr bool DEV = true;
     using S = __half;
     using W = float;
     using R = float;
-    static __device__ __forceinline__ W load(const S *p, R wref) { return wref + wref * __half2float(*p); }
+    static __device__ __forceinline__ W load(const S *p, R wref) { return __builtin_fmaf(wref, __half2float(*p), wref); }
     static __device__ __forceinline__ void store(S *p, R v, R wref) { *p = __float2half_rn(rel_dev(v, wref)); }
 };
 template <>
@@ -197,7 +199,7 @@ struct Prec<SCLBM_BF16DEV> {
     using S = __hip_bfloat16;
     using W = float;
     using R = float;
-    static __device__ __forceinline__ W load(const S *p, R wref) { return wref + wref * __bfloat162float(*p); }
+    static __device__ __forceinline__ W load(const S *p, R wref) { return __builtin_fmaf(wref, __bfloat162float(*p), wref); }
     static __device__ __forceinline__ void store(S *p, R v, R wref) { *p = __float2bfloat16(rel_dev(v, wref)); }
 };
 

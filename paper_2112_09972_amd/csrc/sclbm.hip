@@ -176,6 +176,9 @@ struct sclbm_ctx {
     double *result() { return reinterpret_cast<double *>(ws + lay.result); }
     double *mass_now() { return reinterpret_cast<double *>(ws + lay.mass); }
     double *mass_target() { return reinterpret_cast<double *>(ws + lay.mass) + cfg.nbox; }
+    // One FP64 value per node of every box, between steps: the population buffer that does not hold
+    // the state, which the next step writes in full (76 bytes a node or more).
+    double *scratch_field() { return reinterpret_cast<double *>(fbuf(1 - par)); }
     double *diag() { return reinterpret_cast<double *>(ws + lay.diag); }
     int64_t *clock() { return reinterpret_cast<int64_t *>(ws + lay.clock); }
 };
@@ -1034,19 +1037,20 @@ sclbm_status sclbm_droplet_surface_all(sclbm_ctx *c, double *dev_out) {
     sclbm_status st = check_ctx(c);
     if (st) return st;
     if (!dev_out) return fail(SCLBM_EINVAL, "null output");
-    const int ntx = (c->cfg.nx - 1 + SURF_T - 1) / SURF_T, nty = (c->cfg.ny - 1 + SURF_T - 1) / SURF_T;
-    const int ntiles = ntx * nty;
-    // at most 8 stats blocks' worth of partials per box (2 values each instead of 16)
-    const int nblk = std::min<int>(ntiles, int(8 * stats_blocks(&c->cfg)));
+    // about four nodes a thread; at most 8 stats blocks' worth of partials per box (2 values each instead of 16)
+    const int nblk = int(std::min<int64_t>((c->N + 4 * NRED_THREADS - 1) / (4 * NRED_THREADS), 8 * stats_blocks(&c->cfg)));
+    double *phi = c->scratch_field();
     hipError_t e = by_prec(c->cfg.prec, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
         using S = typename Prec<P>::S;
         const S *f = reinterpret_cast<const S *>(c->fbuf(c->par));
-        hipLaunchKernelGGL((k_surface<P>), dim3(nblk, c->cfg.nbox), dim3(NRED_THREADS), 0, c->stream, f,
-                           c->refbuf(c->par), c->geom, 0, ntx, ntiles, c->partial());
+        hipLaunchKernelGGL((k_phi<P>), dim3(grid1d(c->N, NRED_THREADS), c->cfg.nbox), dim3(NRED_THREADS), 0, c->stream, f,
+                           c->refbuf(c->par), c->geom, phi);
         return hipGetLastError();
     });
     if (e != hipSuccess) return fail(SCLBM_EHIP, "surface kernel: %s", hipGetErrorString(e));
+    k_surface<<<dim3(nblk, c->cfg.nbox), NRED_THREADS, 0, c->stream>>>(phi, c->geom, c->partial());
+    HIP_LAUNCHED();
     hipLaunchKernelGGL((k_final<2>), dim3(c->cfg.nbox), dim3(NRED_THREADS), 0, c->stream, c->partial(), nblk, dev_out);
     HIP_LAUNCHED();
     return SCLBM_OK;
