@@ -437,15 +437,16 @@ sclbm_status launch_stats(sclbm_ctx *c, int32_t b0, int32_t nb, double *partial,
     return SCLBM_OK;
 }
 
-// Droplet mass (sum of rho_A where rho_A > rho_B) of boxes [b0, b0 + nb) into c->mass_now() + b0.
-sclbm_status launch_drop_mass(sclbm_ctx *c, int32_t b0, int32_t nb) {
+// Droplet mass (sum of rho_A where rho_A > rho_B) of boxes [b0, b0 + nb) into c->mass_now() + b0
+// and, with mark, which of their nodes those are ([box][node]).
+sclbm_status launch_drop_mass(sclbm_ctx *c, int32_t b0, int32_t nb, uint8_t *mark = nullptr) {
     const int bpb = int(stats_blocks(&c->cfg));
     hipError_t e = by_prec(c->cfg.prec, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
         using S = typename Prec<P>::S;
         const S *f = reinterpret_cast<const S *>(c->fbuf(c->par));
         hipLaunchKernelGGL((k_drop_mass<P>), dim3(bpb, nb), dim3(NRED_THREADS), 0, c->stream, f, c->refbuf(c->par),
-                           c->geom, b0, c->partial());
+                           c->geom, b0, c->partial(), mark);
         return hipGetLastError();
     });
     if (e != hipSuccess) return fail(SCLBM_EHIP, "droplet mass kernel: %s", hipGetErrorString(e));
@@ -1085,14 +1086,15 @@ sclbm_status sclbm_reinject(sclbm_ctx *c, int32_t box, const double *target_mass
             return fail(SCLBM_EINVAL, "target mass %d must be positive and finite", i);
     HIP_TRY(hipMemcpyAsync(c->mass_target() + b0, target_mass, size_t(nb) * sizeof(double), hipMemcpyHostToDevice,
                            c->stream));
-    if ((st = launch_drop_mass(c, b0, nb))) return st;
+    uint8_t *mark = reinterpret_cast<uint8_t *>(c->scratch_field());
+    if ((st = launch_drop_mass(c, b0, nb, mark))) return st;
     hipError_t e = by_prec(c->cfg.prec, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
         using S = typename Prec<P>::S;
         S *f = reinterpret_cast<S *>(c->fbuf(c->par));
         const unsigned blocks = std::min<unsigned>(grid1d(c->N, 256), 2048u);
         hipLaunchKernelGGL((k_reinject<P>), dim3(blocks, nb), dim3(256), 0, c->stream, f, c->refbuf(c->par), c->geom,
-                           b0, c->mass_now(), c->mass_target());
+                           b0, mark, c->mass_now(), c->mass_target());
         return hipGetLastError();
     });
     if (e != hipSuccess) return fail(SCLBM_EHIP, "reinjection kernel: %s", hipGetErrorString(e));
