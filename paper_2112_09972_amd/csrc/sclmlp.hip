@@ -2,6 +2,7 @@
 // of every call: sclmlp.h.  Kernels: mlp_kernels.hpp.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -50,10 +51,17 @@ sclbm_status fail(sclbm_status st, const char *fmt, ...) {
 constexpr size_t kAlign = 256;
 size_t round_up(size_t v, size_t a = kAlign) { return (v + a - 1) / a * a; }
 
+// Slices of the batch whose weight gradients are summed separately.  Up to 1024 rows 32 x 32
+// tiles give 800 wavefronts and need none; above, a wavefront takes 64 x 64 (half the operand
+// traffic) and the batch is cut into slices of about 1024 rows, at most 8, to have enough of them
+// (8192 rows: all gradients 30 us and their sum 5.5; one 64 x 64 tile per LDS-staging workgroup,
+// layer after layer, with the row sums after each, took 287).
+constexpr int64_t kSmallBatch = 1024;
+int grad_slices(int64_t mpad) { return int(std::min<int64_t>(8, (mpad + kSmallBatch - 1) / kSmallBatch)); }
+
 // Byte offsets of every buffer inside the workspace for batches of up to mmax rows.
 struct Layout {
-    size_t p, g, m1, m2, norm, wb[NLAYER], wbt[NLAYER], wbf[3], x, xt, h[3], ht[3], dza, dzb, dzat, dzbt, dy, partial,
-        loss, bad, total;
+    size_t p, g, m1, m2, norm, wf[3], wtf[3], w4, x, xt, h[3], ht[3], dz[2], dzt[3], dy, partial, part, loss, bad, total;
 };
 
 Layout make_layout(int64_t mmax) {
@@ -70,26 +78,25 @@ Layout make_layout(int64_t mmax) {
     L.m1 = take(pb);
     L.m2 = take(pb);
     L.norm = take(sizeof(float) * (2 * NIN + 2 * NOUT));
-    const int rows[NLAYER] = {NHID, NHID, NHID, NOUT}, cols[NLAYER] = {NIN, NHID, NHID, NHID};
-    for (int l = 0; l < NLAYER; ++l) L.wb[l] = take(sizeof(bf16) * rows[l] * cols[l]);
-    L.wbt[0] = L.wbt[3] = 0;
-    for (int l = 1; l < 3; ++l) L.wbt[l] = take(sizeof(bf16) * NHID * NHID);
-    for (int l = 0; l < 3; ++l) L.wbf[l] = take(sizeof(bf16) * NHID * (l == 0 ? NIN : NHID));
+    for (int l = 0; l < 3; ++l) L.wf[l] = take(sizeof(bf16) * NHID * (l == 0 ? NIN : NHID));
+    for (int l = 0; l < 3; ++l) L.wtf[l] = l == 0 ? 0 : take(sizeof(bf16) * NHID * NHID);
+    L.w4 = take(sizeof(bf16) * NOUT * NHID);
     const size_t m = (size_t)mmax;
     L.x = take(sizeof(bf16) * m * NIN);
     L.xt = take(sizeof(bf16) * m * NIN);
     for (int l = 0; l < 3; ++l) {
         L.h[l] = take(sizeof(bf16) * m * NHID);
         L.ht[l] = take(sizeof(bf16) * m * NHID);
+        L.dzt[l] = take(sizeof(bf16) * m * NHID);
     }
-    L.dza = take(sizeof(bf16) * m * NHID);
-    L.dzb = take(sizeof(bf16) * m * NHID);
-    L.dzat = take(sizeof(bf16) * m * NHID);
-    L.dzbt = take(sizeof(bf16) * m * NHID);
+    for (int l = 0; l < 2; ++l) L.dz[l] = take(sizeof(bf16) * m * NHID);
     L.dy = take(sizeof(float) * m * NOUT);
     L.partial = take(sizeof(double) * 4 * (m / OUT_ROWS));
     L.loss = take(sizeof(double));
     L.bad = take(sizeof(unsigned));
+    L.part = off;
+    const int slices = grad_slices(mmax);
+    if (slices > 1) take(sizeof(float) * slices * OFF_W4);
     L.total = off;
     return L;
 }
@@ -114,76 +121,28 @@ struct sclmlp_ctx {
     float *in_scale() const { return at<float>(lay.norm) + NIN; }
     float *out_shift() const { return at<float>(lay.norm) + 2 * NIN; }
     float *out_scale() const { return at<float>(lay.norm) + 2 * NIN + NOUT; }
-    bf16 *wb(int l) const { return at<bf16>(lay.wb[l]); }
-    bf16 *wbt(int l) const { return at<bf16>(lay.wbt[l]); }
-    bf16 *wbf(int l) const { return at<bf16>(lay.wbf[l]); }
+    bf16 *wf(int l) const { return at<bf16>(lay.wf[l]); }
+    bf16 *wtf(int l) const { return at<bf16>(lay.wtf[l]); }
+    bf16 *w4() const { return at<bf16>(lay.w4); }
     bf16 *h(int l) const { return at<bf16>(lay.h[l]); }
     bf16 *ht(int l) const { return at<bf16>(lay.ht[l]); }
+    bf16 *dz(int l) const { return at<bf16>(lay.dz[l]); }
+    bf16 *dzt(int l) const { return at<bf16>(lay.dzt[l]); }
 };
 
 namespace {
 
-// C = A B^T with the epilogue EPI.  Tiles of 64 x 128 (two waves down, two across, each
-// 32 x 64) when the product has at least 1024 rows, else 64 x 64; K staged 64 columns at a
-// time (measured on the 8192 x 512 x 576 and x 512 products: deeper stages and 128 x 128
-// tiles were slower).
-template <int EPI, bool AF32 = false>
-sclbm_status gemm(const sclmlp_ctx *c, const GemmArgs &g) {
-    if (g.K % 8 != 0 || g.K <= 0 || g.M <= 0 || g.N <= 0)
-        return fail(SCLBM_EINVAL, "gemm shape %d x %d x %d", g.M, g.N, g.K);
-    // 16-byte loads and stores: row strides in whole 8-element groups
-    if (g.lda % 8 || g.ldb % 8 || (EPI != EPI_F32 && ((g.C && g.ldc % 8) || (g.CT && g.ldct % 8))))
-        return fail(SCLBM_EINVAL, "gemm row strides must be multiples of 8");
-    if (g.M >= 1024) {
-        dim3 grid((g.N + 127) / 128, (g.M + 63) / 64);
-        k_gemm_nt<64, 128, 64, EPI, AF32><<<grid, 256, 0, c->stream>>>(g);
-    } else {
-        dim3 grid((g.N + 63) / 64, (g.M + 63) / 64);
-        k_gemm_nt<64, 64, 64, EPI, AF32><<<grid, 256, 0, c->stream>>>(g);
-    }
+// One hidden layer over mpad rows: forward, or with MASK the gradient of the layer below.
+// Up to kSmallBatch rows a wavefront takes one 32 x 32 tile and a workgroup of its own (256 rows: 128
+// of them, 4.1 us a layer; 64 x 64 tiles staged through LDS, 32 workgroups, took 8.6); above,
+// 64 x 64, four to a workgroup, which reads each operand half as often (8192 rows: 11 us).
+template <int K, bool MASK>
+sclbm_status layer(const sclmlp_ctx *c, const LayerArgs &g) {
+    if (g.Mpad <= kSmallBatch)
+        k_layer<K, 1, 1, MASK, 1><<<g.Mpad / 32 * (NHID / 32), 64, 0, c->stream>>>(g);
+    else
+        k_layer<K, 2, 2, MASK, 2><<<g.Mpad / 128 * (NHID / 128), 256, 0, c->stream>>>(g);
     HIP_LAUNCHED();
-    return SCLBM_OK;
-}
-
-GemmArgs gargs(const bf16 *A, int lda, const bf16 *B, int ldb, int M, int N, int K) {
-    GemmArgs g{};
-    g.A = A;
-    g.B = B;
-    g.lda = lda;
-    g.ldb = ldb;
-    g.M = M;
-    g.N = N;
-    g.K = K;
-    return g;
-}
-
-// The three hidden layers (bias + ReLU); with `transposed` also the [unit][row] copies.
-// With `windows` (inference) the first layer reads the n FP32 windows directly and normalises
-// them while staging; otherwise it reads the BF16 inputs the preparation kernel wrote.
-sclbm_status hidden_forward(const sclmlp_ctx *c, int Mp, bool transposed, const float *windows = nullptr,
-                            int n = 0) {
-    const float *P = c->P();
-    const int boff[3] = {OFF_B1, OFF_B2, OFF_B3};
-    for (int l = 0; l < 3; ++l) {
-        const bf16 *A = l == 0 ? c->at<bf16>(c->lay.x) : c->h(l - 1);
-        const int K = l == 0 ? NIN : NHID;
-        GemmArgs g = gargs(A, K, c->wb(l), K, Mp, NHID, K);
-        g.bias = P + boff[l];
-        g.C = c->h(l);
-        g.ldc = NHID;
-        g.CT = transposed ? c->ht(l) : nullptr;
-        g.ldct = Mp;
-        if (l == 0 && windows) {
-            g.A = nullptr;
-            g.Af = windows;
-            g.ashift = c->in_shift();
-            g.ascale = c->in_scale();
-            g.arows = n;
-            TRY((gemm<EPI_RELU, true>(c, g)));
-        } else {
-            TRY(gemm<EPI_RELU>(c, g));
-        }
-    }
     return SCLBM_OK;
 }
 
@@ -193,18 +152,18 @@ AdamArgs adam_args(const sclmlp_ctx *c) {
     a.g = c->G();
     a.m = c->at<float>(c->lay.m1);
     a.v = c->at<float>(c->lay.m2);
-    a.n = NPARAM;
-    a.seg[0] = Seg{OFF_W1, NHID, NIN, c->wb(0), nullptr, c->wbf(0)};
-    a.seg[1] = Seg{OFF_W2, NHID, NHID, c->wb(1), c->wbt(1), c->wbf(1)};
-    a.seg[2] = Seg{OFF_W3, NHID, NHID, c->wb(2), c->wbt(2), c->wbf(2)};
-    a.seg[3] = Seg{OFF_W4, NOUT, NHID, c->wb(3), nullptr, nullptr};
+    for (int l = 0; l < 3; ++l) {
+        a.w[l] = c->wf(l);
+        a.wt[l] = l == 0 ? nullptr : c->wtf(l);
+    }
+    a.w4 = c->w4();
     return a;
 }
 
 sclbm_status refresh_copies(sclmlp_ctx *c) {
     AdamArgs a = adam_args(c);
     a.update = 0;
-    k_adam<<<1024, 256, 0, c->stream>>>(a);
+    k_adam<<<ADAM_BLOCKS, 256, 0, c->stream>>>(a);
     HIP_LAUNCHED();
     return SCLBM_OK;
 }
@@ -240,7 +199,7 @@ sclbm_status sclmlp_create(int64_t max_batch, void *dev_workspace, size_t bytes,
     c->lay = make_layout(c->mmax);
     c->stream = static_cast<hipStream_t>(hip_stream);
     hipError_t e = hipGetDevice(&c->device);
-    if (e == hipSuccess) e = hipMemsetAsync(c->ws, 0, c->lay.total, c->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(c->ws, 0, c->lay.part, c->stream);
     if (e == hipSuccess) {
         std::vector<float> norm(2 * NIN + 2 * NOUT, 0.0f);
         for (int i = 0; i < NIN; ++i) norm[NIN + i] = 1.0f;
@@ -321,45 +280,35 @@ sclbm_status sclmlp_predict(sclmlp_ctx *c, const float *dev_windows, int64_t n, 
     if (n == 0) return SCLBM_OK;
     if (!dev_windows || !dev_out) return fail(SCLBM_EINVAL, "null buffer");
     TRY(use_device(c));
-    const int Mp = (int)padded_rows(n);
-    if (reinterpret_cast<uintptr_t>(dev_windows) % 16 == 0) {
-        // one launch: the four layers, activations in LDS (same results as the layer-by-layer path)
-        ForwardArgs f{};
-        f.win = dev_windows;
-        f.n = (int)n;
-        f.ashift = c->in_shift();
-        f.ascale = c->in_scale();
-        const int boff[3] = {OFF_B1, OFF_B2, OFF_B3};
-        for (int l = 0; l < 3; ++l) {
-            f.W[l] = c->wbf(l);
-            f.bias[l] = c->P() + boff[l];
-        }
-        f.W4 = c->wb(3);
-        f.b4 = c->P() + OFF_B4;
-        f.oshift = c->out_shift();
-        f.oscale = c->out_scale();
-        f.out = dev_out;
-        k_forward<<<Mp / FW_M, FW_T, 0, c->stream>>>(f);
-        HIP_LAUNCHED();
-        return SCLBM_OK;
-    } else {
-        k_prep<false><<<dim3(NIN / 64, Mp / 64), 256, 0, c->stream>>>(dev_windows, nullptr, nullptr, (int)n, (int)n,
-                                                                        c->in_shift(), c->in_scale(),
-                                                                        c->at<bf16>(c->lay.x), nullptr, Mp,
-                                                                        c->at<unsigned>(c->lay.bad));
-        HIP_LAUNCHED();
-        TRY(hidden_forward(c, Mp, false));
+    ForwardArgs f{};
+    f.win = dev_windows;
+    f.n = (int)n;
+    f.ashift = c->in_shift();
+    f.ascale = c->in_scale();
+    const int boff[3] = {OFF_B1, OFF_B2, OFF_B3};
+    for (int l = 0; l < 3; ++l) {
+        f.W[l] = c->wf(l);
+        f.bias[l] = c->P() + boff[l];
     }
-    k_out<true><<<Mp / OUT_ROWS, 256, 0, c->stream>>>(c->h(2), c->wb(3), c->P() + OFF_B4, (int)n, c->out_shift(),
-                                                c->out_scale(), dev_out, nullptr, nullptr, nullptr, 0, nullptr,
-                                                nullptr);
+    f.W4 = c->w4();
+    f.b4 = c->P() + OFF_B4;
+    f.oshift = c->out_shift();
+    f.oscale = c->out_scale();
+    f.out = dev_out;
+    const int blocks = int((n + FW_M - 1) / FW_M);
+    if (reinterpret_cast<uintptr_t>(dev_windows) % 16 == 0)
+        k_forward<true><<<blocks, FW_T, 0, c->stream>>>(f);
+    else
+        k_forward<false><<<blocks, FW_T, 0, c->stream>>>(f);
     HIP_LAUNCHED();
     return SCLBM_OK;
 }
 
-sclbm_status sclmlp_gradients(sclmlp_ctx *c, const float *dev_windows, const float *dev_targets,
-                              const int32_t *dev_index, const int32_t *dev_sym, int64_t n, int64_t ndata,
-                              double *dev_loss) {
+namespace {
+
+// Forward and backward pass, all gradients into the context; with adam->update also the Adam step.
+sclbm_status backward(sclmlp_ctx *c, const float *dev_windows, const float *dev_targets, const int32_t *dev_index,
+                      const int32_t *dev_sym, int64_t n, int64_t ndata, double *dev_loss, const AdamArgs &adam) {
     if (!c) return fail(SCLBM_EINVAL, "null context");
     if (n < 1 || n > c->max_batch) return fail(SCLBM_EINVAL, "n = %lld outside [1, %lld]", (long long)n,
                                               (long long)c->max_batch);
@@ -367,66 +316,76 @@ sclbm_status sclmlp_gradients(sclmlp_ctx *c, const float *dev_windows, const flo
     if (!dev_index && ndata < n) return fail(SCLBM_EINVAL, "without an index ndata must be >= n");
     if (!dev_windows || !dev_targets) return fail(SCLBM_EINVAL, "null buffer");
     TRY(use_device(c));
-    const int Mp = (int)padded_rows(n), nb = Mp / 64, nbo = Mp / OUT_ROWS;
-    float *G = c->G();
-    bf16 *dza = c->at<bf16>(c->lay.dza), *dzb = c->at<bf16>(c->lay.dzb);
-    bf16 *dzat = c->at<bf16>(c->lay.dzat), *dzbt = c->at<bf16>(c->lay.dzbt);
+    const int Mp = (int)padded_rows(n), nbo = Mp / OUT_ROWS;
+    float *P = c->P();
+    bf16 *x = c->at<bf16>(c->lay.x), *xt = c->at<bf16>(c->lay.xt);
     float *dy = c->at<float>(c->lay.dy);
     double *partial = c->at<double>(c->lay.partial);
 
-    k_prep<true><<<dim3(NIN / 64, nb), 256, 0, c->stream>>>(dev_windows, dev_index, dev_sym, (int)n, (int)ndata,
-                                                             c->in_shift(), c->in_scale(), c->at<bf16>(c->lay.x),
-                                                             c->at<bf16>(c->lay.xt), Mp, c->at<unsigned>(c->lay.bad));
+    k_prep<<<Mp / PREP_ROWS, PREP_T, 0, c->stream>>>(dev_windows, dev_index, dev_sym, (int)n, (int)ndata, c->in_shift(),
+                                                  c->in_scale(), x, xt, Mp, c->at<unsigned>(c->lay.bad));
     HIP_LAUNCHED();
-    TRY(hidden_forward(c, Mp, true));
-    k_out<false><<<nbo, 256, 0, c->stream>>>(c->h(2), c->wb(3), c->P() + OFF_B4, (int)n, c->out_shift(),
-                                            c->out_scale(), nullptr, dev_targets, dev_index, dev_sym, (int)ndata, dy,
-                                            partial);
+    TRY((layer<NIN, false>(c, {x, c->wf(0), P + OFF_B1, nullptr, c->h(0), c->ht(0), Mp})));
+    TRY((layer<NHID, false>(c, {c->h(0), c->wf(1), P + OFF_B2, nullptr, c->h(1), c->ht(1), Mp})));
+    TRY((layer<NHID, false>(c, {c->h(1), c->wf(2), P + OFF_B3, nullptr, c->h(2), c->ht(2), Mp})));
+    k_out<<<nbo, 256, 0, c->stream>>>(c->h(2), c->w4(), P + OFF_B4, (int)n, c->out_shift(), c->out_scale(), dev_targets,
+                                      dev_index, dev_sym, (int)ndata, dy, partial, c->dz(0), c->dzt(2), Mp);
     HIP_LAUNCHED();
-    k_loss_final<<<1, 256, 0, c->stream>>>(partial, nbo, (int)n, dev_loss ? dev_loss : c->at<double>(c->lay.loss),
-                                          G + OFF_B4);
-    HIP_LAUNCHED();
+    // dZ2, then dZ1 (of which only the parameter gradients are taken)
+    TRY((layer<NHID, true>(c, {c->dz(0), c->wtf(2), nullptr, c->ht(1), c->dz(1), c->dzt(1), Mp})));
+    TRY((layer<NHID, true>(c, {c->dz(1), c->wtf(1), nullptr, c->ht(0), nullptr, c->dzt(0), Mp})));
 
-    // output layer: dZ3 = (dY W4) * relu'(z3); dW4 = dY^T H3 (db4 came with the loss)
-    k_out_back<<<dim3(NHID / 64, nb), 256, 0, c->stream>>>(dy, c->wb(3), c->h(2), dza, dzat, Mp);
-    HIP_LAUNCHED();
-    k_rowdot<NOUT><<<NHID, 256, 0, c->stream>>>(c->ht(2), Mp, Mp, dy, G + OFF_W4, 1, NHID);
-    HIP_LAUNCHED();
-
-    // hidden layers 3, 2, 1: dW = dZ^T H_prev, db = sum_rows dZ, dZ_prev = (dZ W) * relu'(z_prev)
-    const int woff[3] = {OFF_W1, OFF_W2, OFF_W3}, boff[3] = {OFF_B1, OFF_B2, OFF_B3};
-    bf16 *cur = dza, *curT = dzat, *nxt = dzb, *nxtT = dzbt;
-    for (int l = 2; l >= 0; --l) {
-        const int K = l == 0 ? NIN : NHID;
-        const bf16 *prevT = l == 0 ? c->at<bf16>(c->lay.xt) : c->ht(l - 1);
-        GemmArgs gw = gargs(curT, Mp, prevT, Mp, NHID, K, Mp);
-        gw.C = G + woff[l];
-        gw.ldc = K;
-        TRY(gemm<EPI_F32>(c, gw));
-        k_rowdot<1><<<NHID, 256, 0, c->stream>>>(curT, Mp, Mp, nullptr, G + boff[l], 1, 0);
-        HIP_LAUNCHED();
-        if (l == 0) break;
-        GemmArgs gx = gargs(cur, NHID, c->wbt(l), NHID, Mp, NHID, NHID);
-        gx.mask = c->h(l - 1);
-        gx.ldmask = NHID;
-        gx.C = l - 1 > 0 ? nxt : nullptr;  // the first layer needs only the transposed copy
-        gx.ldc = NHID;
-        gx.CT = nxtT;
-        gx.ldct = Mp;
-        TRY(gemm<EPI_MASK>(c, gx));
-        std::swap(cur, nxt);
-        std::swap(curT, nxtT);
+    GradArgs g{};
+    const bf16 *prev[3] = {xt, c->ht(0), c->ht(1)};
+    for (int l = 0; l < 3; ++l) {
+        g.dzT[l] = c->dzt(l);
+        g.prevT[l] = prev[l];
     }
+    g.hT3 = c->ht(2);
+    g.dY = dy;
+    g.partial = partial;
+    g.npartial = nbo;
+    g.n = (int)n;
+    g.Mpad = Mp;
+    g.loss = dev_loss ? dev_loss : c->at<double>(c->lay.loss);
+    g.ad = adam;
+    if (Mp <= kSmallBatch) {
+        constexpr int tiles = (NHID / 64) * (NIN / 64 + 2 * (NHID / 64));
+        g.slices = 1;
+        g.per = Mp / 16;
+        if (adam.update)
+            k_grad<1, 1, true><<<tiles + GRAD_SUMS + 1, 256, 0, c->stream>>>(g);
+        else
+            k_grad<1, 1, false><<<tiles + GRAD_SUMS + 1, 256, 0, c->stream>>>(g);
+        HIP_LAUNCHED();
+        return SCLBM_OK;
+    }
+    constexpr int tiles = (NHID / 256) * (NIN / 64 + 2 * (NHID / 64));
+    g.slices = grad_slices(Mp);
+    g.per = (Mp / 16 + g.slices - 1) / g.slices;
+    g.slices = (Mp / 16 + g.per - 1) / g.per;  // no empty slice
+    g.part = c->at<float>(c->lay.part);
+    k_grad<2, 2, false><<<tiles * g.slices + GRAD_SUMS + 1, 256, 0, c->stream>>>(g);
+    HIP_LAUNCHED();
+    if (adam.update) {
+        AdamArgs a = adam;
+        a.part = g.part;
+        a.slices = g.slices;
+        k_adam<<<ADAM_BLOCKS, 256, 0, c->stream>>>(a);
+    } else {
+        k_sum<<<(OFF_W4 / 4 + 255) / 256, 256, 0, c->stream>>>(g.part, g.slices, adam.g);
+    }
+    HIP_LAUNCHED();
     return SCLBM_OK;
 }
 
-sclbm_status sclmlp_adam(sclmlp_ctx *c, float lr, float beta1, float beta2, float eps) {
+// The next Adam step's arguments.
+sclbm_status adam_next(const sclmlp_ctx *c, float lr, float beta1, float beta2, float eps, AdamArgs &a) {
     if (!c) return fail(SCLBM_EINVAL, "null context");
     if (!(lr > 0.0f) || !(beta1 >= 0.0f && beta1 < 1.0f) || !(beta2 >= 0.0f && beta2 < 1.0f) || !(eps > 0.0f))
         return fail(SCLBM_EINVAL, "Adam hyper-parameters out of range");
-    TRY(use_device(c));
     const int64_t t = c->step + 1;
-    AdamArgs a = adam_args(c);
+    a = adam_args(c);
     a.update = 1;
     a.lr = lr;
     a.beta1 = beta1;
@@ -434,20 +393,36 @@ sclbm_status sclmlp_adam(sclmlp_ctx *c, float lr, float beta1, float beta2, floa
     a.eps = eps;
     a.bc1 = (float)(1.0 - std::pow((double)beta1, (double)t));
     a.bc2 = (float)(1.0 - std::pow((double)beta2, (double)t));
-    k_adam<<<1024, 256, 0, c->stream>>>(a);
+    return SCLBM_OK;
+}
+
+}  // namespace
+
+sclbm_status sclmlp_gradients(sclmlp_ctx *c, const float *dev_windows, const float *dev_targets,
+                              const int32_t *dev_index, const int32_t *dev_sym, int64_t n, int64_t ndata,
+                              double *dev_loss) {
+    if (!c) return fail(SCLBM_EINVAL, "null context");
+    return backward(c, dev_windows, dev_targets, dev_index, dev_sym, n, ndata, dev_loss, adam_args(c));
+}
+
+sclbm_status sclmlp_adam(sclmlp_ctx *c, float lr, float beta1, float beta2, float eps) {
+    AdamArgs a;
+    TRY(adam_next(c, lr, beta1, beta2, eps, a));
+    TRY(use_device(c));
+    k_adam<<<ADAM_BLOCKS, 256, 0, c->stream>>>(a);
     HIP_LAUNCHED();
-    c->step = t;
+    c->step += 1;
     return SCLBM_OK;
 }
 
 sclbm_status sclmlp_train_step(sclmlp_ctx *c, const float *dev_windows, const float *dev_targets,
                                const int32_t *dev_index, const int32_t *dev_sym, int64_t n, int64_t ndata, float lr,
                                float beta1, float beta2, float eps, double *dev_loss) {
-    if (!c) return fail(SCLBM_EINVAL, "null context");
-    if (!(lr > 0.0f) || !(beta1 >= 0.0f && beta1 < 1.0f) || !(beta2 >= 0.0f && beta2 < 1.0f) || !(eps > 0.0f))
-        return fail(SCLBM_EINVAL, "Adam hyper-parameters out of range");
-    TRY(sclmlp_gradients(c, dev_windows, dev_targets, dev_index, dev_sym, n, ndata, dev_loss));
-    return sclmlp_adam(c, lr, beta1, beta2, eps);
+    AdamArgs a;
+    TRY(adam_next(c, lr, beta1, beta2, eps, a));
+    TRY(backward(c, dev_windows, dev_targets, dev_index, dev_sym, n, ndata, dev_loss, a));
+    c->step += 1;
+    return SCLBM_OK;
 }
 
 sclbm_status sclmlp_get_step(const sclmlp_ctx *c, int64_t *step) {

@@ -266,3 +266,36 @@ def test_errors(env):
     bad[5] = np.nan
     with pytest.raises(sc.SclbmError):
         net.set_params(bad)
+
+
+@pytest.mark.parametrize("n", [1, 31, 128, 129, 1024, 1025, 2300])
+def test_gradients_and_fused_step_over_batch_sizes(env, n):
+    """Batches at the edges of the 128-row padding and of the two tilings (one
+    32 x 32 tile a wavefront up to 1024 rows; 64 x 64 with the batch cut into
+    slices above), gathered and mapped: gradients against the FP64 reference with
+    the same storage (bounds of the file's head), and one training step equal, bit
+    for bit, to the gradients followed by Adam."""
+    torch, mlp = env
+    rng = np.random.default_rng(n)
+    w, t = make_batch(30 + n, 700)
+    idx = rng.integers(0, 700, n).astype(np.int32)
+    dev = [torch.from_numpy(v).cuda() for v in (w, t, idx, np.zeros(n, np.int32))]
+    nets = [setup_net(torch, mlp, 19, max_batch=max(n, 200)) for _ in range(2)]
+    (net, p), (other, _) = nets
+    loss = net.gradients(*dev).item()
+    tn = (t[idx].astype(np.float64) - OUT_SHIFT) * OUT_SCALE
+    l_ref, g_ref = ref.backward(rounded_params(p), w[idx].astype(np.float64), tn, round_hidden=ref.round_bf16,
+                                round_grad=ref.round_bf16)
+    assert loss == pytest.approx(l_ref, rel=5e-3)
+    check_grads(net.grads().astype(np.float64), g_ref, 2e-2, "n=%d" % n)
+    dev[3] = torch.from_numpy(rng.integers(0, 48, n).astype(np.int32)).cuda()
+    for _ in range(2):
+        net.gradients(*dev)
+        net.adam(1e-3)
+        other.train_step(*dev, lr=1e-3)
+        assert np.array_equal(net.grads(), other.grads())
+        assert np.array_equal(net.params(), other.params())
+    assert net.step_count == other.step_count == 2
+    # the BF16 copies of both orders follow: the next forward and backward agree too
+    assert net.gradients(*dev).item() == other.gradients(*dev).item()
+    assert np.array_equal(net.grads(), other.grads())
