@@ -56,8 +56,8 @@ size_t round_up(size_t v, size_t a = kAlign) { return (v + a - 1) / a * a; }
 // traffic) and the batch is cut into slices of about 1024 rows, at most 8, to have enough of them
 // (8192 rows: all gradients 30 us and their sum 5.5; one 64 x 64 tile per LDS-staging workgroup,
 // layer after layer, with the row sums after each, took 287).
-constexpr int64_t kSmallBatch = 1024;
-int grad_slices(int64_t mpad) { return int(std::min<int64_t>(8, (mpad + kSmallBatch - 1) / kSmallBatch)); }
+constexpr int64_t kSmallBatch = 2048;
+int grad_slices(int64_t mpad) { return mpad <= kSmallBatch ? 1 : int(std::min<int64_t>(8, (mpad + 1023) / 1024)); }
 
 // Byte offsets of every buffer inside the workspace for batches of up to mmax rows.
 struct Layout {
@@ -136,10 +136,13 @@ namespace {
 // Up to kSmallBatch rows a wavefront takes one 32 x 32 tile and a workgroup of its own (256 rows: 128
 // of them, 4.1 us a layer; 64 x 64 tiles staged through LDS, 32 workgroups, took 8.6); above,
 // 64 x 64, four to a workgroup, which reads each operand half as often (8192 rows: 11 us).
+
 template <int K, bool MASK>
 sclbm_status layer(const sclmlp_ctx *c, const LayerArgs &g) {
     if (g.Mpad <= kSmallBatch)
         k_layer<K, 1, 1, MASK, 1><<<g.Mpad / 32 * (NHID / 32), 64, 0, c->stream>>>(g);
+    else if (g.Mpad <= 2 * kSmallBatch)
+        k_layer<K, 2, 1, MASK, 2><<<g.Mpad / 128 * (NHID / 64), 256, 0, c->stream>>>(g);
     else
         k_layer<K, 2, 2, MASK, 2><<<g.Mpad / 128 * (NHID / 128), 256, 0, c->stream>>>(g);
     HIP_LAUNCHED();
