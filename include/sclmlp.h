@@ -56,6 +56,14 @@ sclbm_status sclmlp_workspace_bytes(int64_t max_batch, size_t *bytes);
 sclbm_status sclmlp_create(int64_t max_batch, void *dev_workspace, size_t bytes, void *hip_stream, sclmlp_ctx **out);
 sclbm_status sclmlp_destroy(sclmlp_ctx *ctx);
 
+/* Library infrastructure: order the context against another stream of its device (NULL: the null
+ * stream).  after_stream: what the context enqueues from now on waits for the work that
+ * hip_stream holds now (the producers of its inputs).  before_stream: what is enqueued on
+ * hip_stream from now on waits for the context's work so far (its results).  Neither waits on
+ * the host; with the context's own stream they do nothing. */
+sclbm_status sclmlp_after_stream(sclmlp_ctx *ctx, void *hip_stream);
+sclbm_status sclmlp_before_stream(sclmlp_ctx *ctx, void *hip_stream);
+
 /* Load all SCLMLP_NPARAM parameters (host FP32, layout above), refresh the BF16
  * copies and reset Adam (moments to zero, step counter to zero).  Synchronises. */
 sclbm_status sclmlp_set_params(sclmlp_ctx *ctx, const float *params);

@@ -116,6 +116,8 @@ def _load_library():
         "sclmlp_workspace_bytes": [I64, ctypes.POINTER(ctypes.c_size_t)],
         "sclmlp_create": [I64, P, ctypes.c_size_t, P, ctypes.POINTER(P)],
         "sclmlp_destroy": [P],
+        "sclmlp_after_stream": [P, P],
+        "sclmlp_before_stream": [P, P],
         "sclmlp_set_params": [P, P],
         "sclmlp_get_params": [P, P],
         "sclmlp_get_grads": [P, P],

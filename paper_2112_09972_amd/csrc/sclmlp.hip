@@ -61,7 +61,7 @@ int grad_slices(int64_t mpad) { return mpad <= kSmallBatch ? 1 : int(std::min<in
 
 // Byte offsets of every buffer inside the workspace for batches of up to mmax rows.
 struct Layout {
-    size_t p, g, m1, m2, norm, wf[3], wtf[3], w4, x, xt, h[3], ht[3], dz[2], dzt[3], dy, partial, part, loss, bad, total;
+    size_t p, g, m1, m2, norm, wf[3], wtf[3], w4, x, xt, h[3], ht[3], dz[2], dzt[3], dy, partial, part, loss, bad, zeroed, total;
 };
 
 Layout make_layout(int64_t mmax) {
@@ -81,22 +81,26 @@ Layout make_layout(int64_t mmax) {
     for (int l = 0; l < 3; ++l) L.wf[l] = take(sizeof(bf16) * NHID * (l == 0 ? NIN : NHID));
     for (int l = 0; l < 3; ++l) L.wtf[l] = l == 0 ? 0 : take(sizeof(bf16) * NHID * NHID);
     L.w4 = take(sizeof(bf16) * NOUT * NHID);
+    L.loss = take(sizeof(double));
+    L.bad = take(sizeof(unsigned));
+    L.zeroed = off;
     const size_t m = (size_t)mmax;
     L.x = take(sizeof(bf16) * m * NIN);
+    for (int l = 0; l < 3; ++l) L.h[l] = take(sizeof(bf16) * m * NHID);
+    // the pre-activation gradients over the units take the place of activations whose last
+    // reader has run (dZ3 that of H3, which its kernel reads in the same place), and the
+    // slices of the weight gradients that of X and all of them
+    L.dz[0] = L.h[2];
+    L.dz[1] = L.h[1];
+    L.part = L.x;
+    off = std::max(off, round_up(L.part + sizeof(float) * grad_slices(mmax) * OFF_W4));
     L.xt = take(sizeof(bf16) * m * NIN);
     for (int l = 0; l < 3; ++l) {
-        L.h[l] = take(sizeof(bf16) * m * NHID);
         L.ht[l] = take(sizeof(bf16) * m * NHID);
         L.dzt[l] = take(sizeof(bf16) * m * NHID);
     }
-    for (int l = 0; l < 2; ++l) L.dz[l] = take(sizeof(bf16) * m * NHID);
     L.dy = take(sizeof(float) * m * NOUT);
     L.partial = take(sizeof(double) * 4 * (m / OUT_ROWS));
-    L.loss = take(sizeof(double));
-    L.bad = take(sizeof(unsigned));
-    L.part = off;
-    const int slices = grad_slices(mmax);
-    if (slices > 1) take(sizeof(float) * slices * OFF_W4);
     L.total = off;
     return L;
 }
@@ -112,6 +116,7 @@ struct sclmlp_ctx {
     hipStream_t stream = nullptr;
     int device = 0;
     int64_t step = 0;
+    hipEvent_t inputs = nullptr, results = nullptr;  // order against another stream (no timing)
 
     template <class T>
     T *at(size_t off) const { return reinterpret_cast<T *>(ws + off); }
@@ -202,7 +207,9 @@ sclbm_status sclmlp_create(int64_t max_batch, void *dev_workspace, size_t bytes,
     c->lay = make_layout(c->mmax);
     c->stream = static_cast<hipStream_t>(hip_stream);
     hipError_t e = hipGetDevice(&c->device);
-    if (e == hipSuccess) e = hipMemsetAsync(c->ws, 0, c->lay.part, c->stream);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&c->inputs, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&c->results, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipMemsetAsync(c->ws, 0, c->lay.zeroed, c->stream);
     if (e == hipSuccess) {
         std::vector<float> norm(2 * NIN + 2 * NOUT, 0.0f);
         for (int i = 0; i < NIN; ++i) norm[NIN + i] = 1.0f;
@@ -211,7 +218,7 @@ sclbm_status sclmlp_create(int64_t max_batch, void *dev_workspace, size_t bytes,
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     }
     if (e != hipSuccess) {
-        delete c;
+        sclmlp_destroy(c);
         return fail(SCLBM_EHIP, "create: %s", hipGetErrorString(e));
     }
     *out = c;
@@ -219,7 +226,31 @@ sclbm_status sclmlp_create(int64_t max_batch, void *dev_workspace, size_t bytes,
 }
 
 sclbm_status sclmlp_destroy(sclmlp_ctx *ctx) {
+    if (ctx) {
+        if (ctx->inputs) (void)hipEventDestroy(ctx->inputs);  // teardown: nothing to do on failure
+        if (ctx->results) (void)hipEventDestroy(ctx->results);
+    }
     delete ctx;
+    return SCLBM_OK;
+}
+
+sclbm_status sclmlp_after_stream(sclmlp_ctx *c, void *hip_stream) {
+    if (!c) return fail(SCLBM_EINVAL, "null context");
+    hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    if (s == c->stream) return SCLBM_OK;
+    TRY(use_device(c));
+    HIP_TRY(hipEventRecord(c->inputs, s));
+    HIP_TRY(hipStreamWaitEvent(c->stream, c->inputs, 0));
+    return SCLBM_OK;
+}
+
+sclbm_status sclmlp_before_stream(sclmlp_ctx *c, void *hip_stream) {
+    if (!c) return fail(SCLBM_EINVAL, "null context");
+    hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    if (s == c->stream) return SCLBM_OK;
+    TRY(use_device(c));
+    HIP_TRY(hipEventRecord(c->results, c->stream));
+    HIP_TRY(hipStreamWaitEvent(s, c->results, 0));
     return SCLBM_OK;
 }
 

@@ -143,12 +143,15 @@ class Network:
         except Exception:
             pass
 
-    def _sync_torch(self):
-        self.stream.wait_stream(self.torch.cuda.current_stream(self.device))
+    def _sync_torch(self) -> int:
+        """The context waits for torch's current stream (the inputs' producers); returns that stream's handle."""
+        cur = self.torch.cuda.current_stream(self.device).cuda_stream
+        _check(_lib.sclmlp_after_stream(self.ctx, cur))
+        return cur
 
-    def _done(self, *tensors):
+    def _done(self, cur: int, *tensors):
         # results are produced on the context's stream; let torch's stream wait for them
-        self.torch.cuda.current_stream(self.device).wait_stream(self.stream)
+        _check(_lib.sclmlp_before_stream(self.ctx, cur))
         for t in tensors:
             if t is not None:
                 t.record_stream(self.stream)
@@ -176,20 +179,25 @@ class Network:
         """windows: float32 [n][576] device tensor (n may exceed max_batch: chunked)."""
         torch = self.torch
         n = windows.shape[0]
-        if out is None:
+        given = out is not None
+        if not given:
             out = torch.empty((n, NOUT), dtype=torch.float32, device=self.device)
-        self._sync_torch()
-        for s in range(0, n, self.max_batch):
-            e = min(n, s + self.max_batch)
-            sclmlp_predict(self.ctx, windows[s:e], e - s, out[s:e])
-        self._done(windows, out)
+        cur = self._sync_torch()
+        if n <= self.max_batch:
+            sclmlp_predict(self.ctx, windows, n, out)
+        else:
+            for s in range(0, n, self.max_batch):
+                e = min(n, s + self.max_batch)
+                sclmlp_predict(self.ctx, windows[s:e], e - s, out[s:e])
+        # (an output allocated here belongs to torch's current stream, which waits)
+        self._done(cur, windows, out if given else None)
         return out
 
     def gradients(self, windows, targets, index=None, sym=None, n=None):
         n = (index.shape[0] if index is not None else windows.shape[0]) if n is None else n
-        self._sync_torch()
+        cur = self._sync_torch()
         sclmlp_gradients(self.ctx, windows, targets, index, sym, n, windows.shape[0], self.loss_buf)
-        self._done(windows, targets, index, sym)
+        self._done(cur, windows, targets, index, sym)
         return self.loss_buf
 
     def adam(self, lr, beta1=0.9, beta2=0.999, eps=1e-8):
@@ -197,8 +205,8 @@ class Network:
 
     def train_step(self, windows, targets, index=None, sym=None, n=None, lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8):
         n = (index.shape[0] if index is not None else windows.shape[0]) if n is None else n
-        self._sync_torch()
+        cur = self._sync_torch()
         sclmlp_train_step(self.ctx, windows, targets, index, sym, n, windows.shape[0], lr, beta1, beta2, eps,
                           self.loss_buf)
-        self._done(windows, targets, index, sym)
+        self._done(cur, windows, targets, index, sym)
         return self.loss_buf
