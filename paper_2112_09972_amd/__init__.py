@@ -59,7 +59,8 @@ EXPORTS = [
     "sclbm_droplet_moments_all_static", "sclbm_set_gradient", "sclbm_init_uniform", "sclbm_set_health_check",
     "sclbm_mm_semi_axes",
     # droplet-shape surrogate (sclmlp.h)
-    "sclmlp_workspace_bytes", "sclmlp_create", "sclmlp_destroy", "sclmlp_set_params", "sclmlp_get_params",
+    "sclmlp_workspace_bytes", "sclmlp_create", "sclmlp_destroy", "sclmlp_after_stream", "sclmlp_before_stream",
+    "sclmlp_set_params", "sclmlp_get_params",
     "sclmlp_get_grads", "sclmlp_set_normalization", "sclmlp_predict", "sclmlp_gradients", "sclmlp_adam",
     "sclmlp_train_step", "sclmlp_get_step", "sclmlp_bad_rows", "sclmlp_last_error",
 ]
