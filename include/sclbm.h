@@ -287,8 +287,9 @@ sclbm_status sclbm_load(sclbm_ctx *ctx, const void *host_buf, size_t bytes);
  * 1..64); the 16-bit formats take (4, 4) where the row's last 256-wide tile is
  * full or holds more than 160 nodes.  The default z-chunk minimises (rounds of
  * resident workgroups) x (planes per chunk + 2), at most 64 planes for the
- * 16-bit formats.  The shape only
- * changes speed, never results.  Pointers of get_launch may be NULL. */
+ * 16-bit formats.  Where the default shape would leave many lanes beyond the row's end, tiles
+ * fitted to the row run in its place (an autotuner candidate like any other, reported as
+ * the default shape); every other shape runs as given.  The shape only changes speed, never results.  Pointers of get_launch may be NULL. */
 sclbm_status sclbm_set_launch(sclbm_ctx *ctx, int32_t tile_rows, int32_t zchunk, int32_t tile_waves);
 sclbm_status sclbm_get_launch(const sclbm_ctx *ctx, int32_t *tile_rows, int32_t *zchunk, int32_t *tile_waves);
 

@@ -97,11 +97,15 @@ __host__ __device__ constexpr R w_of(int i) {
 // 32-bit byte offset per lane.  Word 3 = 0x00020000 is the raw 32-bit-element
 // layout of the gfx9 family.
 using rsrc_t = __amdgpu_buffer_rsrc_t;
-// Cache policy of the population stores: non-temporal (streaming).  Every
-// population is written once per step and read only in the next launch; keeping
-// the stores out of L2's working set leaves it to the rows that neighbouring
-// tiles read again (measured: 12 % fewer HBM reads, 3 % faster step).
+// Cache policies of the population stores.  Non-temporal (streaming): every population is
+// written once per step and read only in the next launch; keeping the stores out of L2's
+// working set leaves it to the rows that neighbouring tiles read again (measured: 12 %
+// fewer HBM reads, 3 % faster step at 128^3 FP32).  Cached: where rows do not start on a cache
+// line, a line is completed by two stores (of neighbouring directions or wavefronts) some
+// time apart, and a streaming store sends each part to memory by itself.  The host chooses
+// (cached_stores).
 constexpr int kStoreNT = 2;
+constexpr int kStoreCached = 0;
 // The same hint on the loads of rows that no other workgroup reads (interior
 // rows of a tile holding whole rows, on planes inside its z-chunk): they are read
 // once per step, and streaming them leaves L2 to the rows that are read twice.
@@ -140,11 +144,9 @@ struct Prec<SCLBM_F64> {
     }
     static __device__ __forceinline__ W dec(L raw, R /*wref*/) { return __builtin_bit_cast(double, raw); }
     static __device__ __forceinline__ B enc(R v, R /*wref*/) { return __builtin_bit_cast(uint64_t, v); }
+    template <int AUX>
     static __device__ __forceinline__ void bstore_bits(rsrc_t r, uint32_t vo, uint32_t so, B b) {
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, b), r, vo, so, kStoreNT);
-    }
-    static __device__ __forceinline__ void bstore(rsrc_t r, uint32_t vo, uint32_t so, R v, R wref) {
-        bstore_bits(r, vo, so, enc(v, wref));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, b), r, vo, so, AUX);
     }
 };
 // FP32 storage; RT the arithmetic type (FP32 for SCLBM_F32, FP64 for SCLBM_F32D).
@@ -168,11 +170,9 @@ struct PrecF32 {
     }
     static __device__ __forceinline__ W dec(L raw, R /*wref*/) { return __builtin_bit_cast(float, raw); }
     static __device__ __forceinline__ B enc(R v, R /*wref*/) { return __builtin_bit_cast(uint32_t, float(v)); }
+    template <int AUX>
     static __device__ __forceinline__ void bstore_bits(rsrc_t r, uint32_t vo, uint32_t so, B b) {
-        __builtin_amdgcn_raw_buffer_store_b32(b, r, vo, so, kStoreNT);
-    }
-    static __device__ __forceinline__ void bstore(rsrc_t r, uint32_t vo, uint32_t so, R v, R wref) {
-        bstore_bits(r, vo, so, enc(v, wref));
+        __builtin_amdgcn_raw_buffer_store_b32(b, r, vo, so, AUX);
     }
 };
 template <>

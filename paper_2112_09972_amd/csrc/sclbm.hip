@@ -156,6 +156,8 @@ struct sclbm_ctx {
     int tile_rows;    // TY
     int tile_waves;   // WX: wavefronts per tile row (tile width 64 WX)
     int zchunk;
+    int def_rows = 0, def_waves = 0, def_zc = 0;  // the default launch shape
+    int fit_w = 0, fit_h = 0, fit_zc = 0;         // fitted tiles that run in its place (0: none)
     std::vector<int64_t> tab_first, tab_len;  // host copies, per box
     // captured step loop: valid for (graph_steps, graph_par, graph_ty, graph_wx, graph_zc)
     hipGraphExec_t graph_exec = nullptr;
@@ -240,12 +242,10 @@ void default_tile(const sclbm_config &c, int &ty, int &wx) {
 // 288^3 1110-1118 / 1081, 64 boxes of 64^3 548 / 552, 8 boxes of 128^3 571-575 /
 // 554-559; longer chunks lose: 256^3 in one 256-wide tile per row needs 256
 // workgroups of 64 planes to fill the device once).
-int default_zchunk(const sclbm_config &c, int ty, int wx) {
-    const long tiles = long((c.nx + 64 * wx - 1) / (64 * wx)) * long((c.ny + ty - 1) / ty) * c.nbox;
-    const bool dev = is_dev(c.prec);
-    const long resident = (dev ? 1024L * kDevWaves : 2048L) / (ty * wx);
-    const long zmax = dev ? 64 : c.nz;
-    long best_cost = -1, best_zc = std::min<long>(c.nz, zmax);
+int best_zchunk(const sclbm_config &c, long tiles, long resident, long &best_cost) {
+    const long zmax = is_dev(c.prec) ? 64 : c.nz;
+    long best_zc = std::min<long>(c.nz, zmax);
+    best_cost = -1;
     for (long nzc = 1; nzc <= std::max(1, c.nz / 2); ++nzc) {
         const long zc = (c.nz + nzc - 1) / nzc;
         if (zc > zmax) continue;
@@ -259,6 +259,15 @@ int default_zchunk(const sclbm_config &c, int ty, int wx) {
     }
     return int(best_zc);
 }
+// Workgroups of `waves` wavefronts resident at a time.
+long resident_groups(const sclbm_config &c, int waves) { return (is_dev(c.prec) ? 1024L * kDevWaves : 2048L) / waves; }
+int default_zchunk(const sclbm_config &c, int ty, int wx, long *cost = nullptr) {
+    const long tiles = long((c.nx + 64 * wx - 1) / (64 * wx)) * long((c.ny + ty - 1) / ty) * c.nbox;
+    long co;
+    const int zc = best_zchunk(c, tiles, resident_groups(c, ty * wx), co);
+    if (cost) *cost = co;
+    return zc;
+}
 
 // The z-chunk that puts all workgroups of a launch in one round of resident
 // workgroups with as many chunks as fit (0 where even whole-box chunks need more
@@ -268,42 +277,101 @@ int default_zchunk(const sclbm_config &c, int ty, int wx) {
 // with 112-plane chunks on 128 x 4 tiles).
 int one_round_zchunk(const sclbm_config &c, int ty, int wx) {
     const long tiles = long((c.nx + 64 * wx - 1) / (64 * wx)) * long((c.ny + ty - 1) / ty) * c.nbox;
-    const long resident = (is_dev(c.prec) ? 1024L * kDevWaves : 2048L) / (ty * wx);
+    const long resident = resident_groups(c, ty * wx);
     const long nzc = std::min<long>(resident / tiles, c.nz);
     if (nzc < 1) return 0;
     return int((c.nz + nzc - 1) / nzc);
 }
 
-// Launch of the step kernel for precision P and a tile of TY rows of WX wavefronts.
-template <int P, int TY, int WX>
+// Fitted tiles for this configuration (w = 0: none): the row, or an equal part of it, wide, and as
+// many rows as FIT_WAVES wavefronts hold.  Chosen where the rounds model above puts them
+// at least 8 % ahead of the default tile, each further tile of a row counting 10 % (ring
+// columns that are one node wide, and stores that end inside a cache line).  Measured, us per
+// step, default tile -> fitted, both with the better store policy: FP32 130^3 248 -> 203 (44 x 11),
+// 150^3 370 -> 278 (75 x 6), 200^3 760 -> 587 (100 x 5); FP64 100 x 120 x 90 periodic 181 -> 172 (100 x 5);
+// BF16 150 x 93 x 67 51 -> 46 (50 x 10), 35 boxes of 21 x 89 x 20 147 -> 96 (21 x 24).  Without the
+// margin they lose where the row fills its tile (FP32 127-wide 79 -> 81, 57 x 48 x 196 40 -> 45:
+// the row pitch is not a constant any more), and without the 10 % where a row is cut into many
+// narrow tiles (FP64 223 x 111 x 52 in seven 209 -> 230).  FP64 arithmetic on FP32 storage spills with them.
+void default_fit(const sclbm_config &c, int &w, int &h, int &zc) {
+    w = h = zc = 0;
+    if (c.prec == SCLBM_F32D) return;
+    int ty, wx;
+    default_tile(c, ty, wx);
+    long cost;
+    default_zchunk(c, ty, wx, &cost);
+    double best = 0.92 * double(cost) * (1.0 + 0.1 * ((c.nx - 1) / (64 * wx)));
+    for (int ntx = 1; ntx <= 8; ++ntx) {
+        const int fw = (c.nx + ntx - 1) / ntx;
+        int fh = std::min(64 * FIT_WAVES / fw, FIT_ROWS);
+        while (fh > 0 && !fit_ok(fw, fh)) --fh;
+        if (fh < 1) continue;
+        const long tiles = long((c.nx + fw - 1) / fw) * long((c.ny + fh - 1) / fh) * c.nbox;
+        const int z = best_zchunk(c, tiles, resident_groups(c, FIT_WAVES), cost);
+        if (double(cost) * (1.0 + 0.1 * (ntx - 1)) > best) continue;
+        best = std::nextafter(double(cost) * (1.0 + 0.1 * (ntx - 1)), 0.0);
+        w = fw;
+        h = fh;
+        zc = z;
+    }
+}
+
+// Store policy of a launch with tiles w nodes wide: cached where the rows' runs of one direction
+// do not start on cache lines.  Then a line's two parts are written some time apart, and streaming
+// stores send each to memory by itself.  Measured, us per step, streaming -> cached: FP32 97 x 124 x 90
+// 93 -> 88, 190^3 783 -> 623; BF16 150 x 93 x 67 59 -> 49; 144 x 69 x 145 79 -> 66.  On whole lines the cached
+// ones cost L2 the rows that are read again: FP32 128^3 126 -> 134, FP64 96 x 125 x 90 153 -> 165.  Two cases
+// between: FP64 rows of even length (FP64 90^3 125 -> 130, 72^3 71 -> 61) and the 256-wide tile of the 16-bit
+// formats (200^3 330 -> 341, 222 x 49 x 64 38 -> 35) gain only while both population buffers fit
+// the 256 MB memory-side cache, or, FP64, where tiles cut the rows (150^3 658 -> 615).
+bool cached_stores(const sclbm_config &c, int w) {
+    const bool dev = is_dev(c.prec);
+    if (c.nx * (dev ? 4 : int(elem_bytes(c.prec))) % 128 == 0) return false;
+    const double state = double(c.nx) * c.ny * c.nz * c.nbox * 2 * Q * elem_bytes(c.prec);
+    if (2.0 * state <= double(256 << 20)) return true;
+    if (c.prec == SCLBM_F64) return c.nx % 2 != 0 || w < c.nx;
+    return !(dev && w >= 256);
+}
+
+// Launch of the step kernel for precision P, a tile of TY rows of WX wavefronts (TY = 0: fitted tiles of
+// WX wavefronts, a.tile_w x a.tile_h nodes) and store policy ST.
+template <int P, int TY, int WX, int ST>
 hipError_t launch_step_tile(sclbm_ctx *c, const StepArgs &a) {
-    dim3 block(64 * WX, TY, 1);
-    dim3 grid((c->cfg.nx + 64 * WX - 1) / (64 * WX), (c->cfg.ny + TY - 1) / TY, a.nzc * c->cfg.nbox);
-    // register budget: two waves per SIMD (up to 256 VGPRs); a tighter budget spills
+    const int w = TY ? 64 * WX : a.tile_w, h = TY ? TY : a.tile_h;
+    const dim3 block = TY ? dim3(64 * WX, TY, 1) : dim3(64 * WX, 1, 1);
+    const dim3 grid((c->cfg.nx + w - 1) / w, (c->cfg.ny + h - 1) / h, a.nzc * c->cfg.nbox);
+    // register budget: two waves per SIMD (up to 256 VGPRs; a tighter budget spills); the 16-bit
+    // formats fit four (128 VGPRs)
     constexpr int WAVES = 2;
     if constexpr (Prec<P>::DEV) {
-        // the 16-bit formats fit four waves per SIMD (128 VGPRs)
         if (c->cfg.bc == SCLBM_BC_GHOST)
-            hipLaunchKernelGGL((k_step_dev<P, TY, WX, true, kDevWaves>), grid, block, 0, c->stream, a);
+            hipLaunchKernelGGL((k_step_dev<P, TY, WX, true, kDevWaves, ST>), grid, block, 0, c->stream, a);
         else
-            hipLaunchKernelGGL((k_step_dev<P, TY, WX, false, kDevWaves>), grid, block, 0, c->stream, a);
+            hipLaunchKernelGGL((k_step_dev<P, TY, WX, false, kDevWaves, ST>), grid, block, 0, c->stream, a);
     } else {
         if (c->cfg.bc == SCLBM_BC_GHOST)
-            hipLaunchKernelGGL((k_step<P, TY, WX, true, WAVES>), grid, block, 0, c->stream, a);
+            hipLaunchKernelGGL((k_step<P, TY, WX, true, WAVES, ST>), grid, block, 0, c->stream, a);
         else
-            hipLaunchKernelGGL((k_step<P, TY, WX, false, WAVES>), grid, block, 0, c->stream, a);
+            hipLaunchKernelGGL((k_step<P, TY, WX, false, WAVES, ST>), grid, block, 0, c->stream, a);
     }
     return hipGetLastError();
 }
 
+template <int P, int ST>
+hipError_t launch_step_st(sclbm_ctx *c, const StepArgs &a) {
+    if (a.tile_w) return launch_step_tile<P, 0, FIT_WAVES, ST>(c, a);
+    if constexpr (Prec<P>::DEV) {
+        if (c->tile_waves == 4) return launch_step_tile<P, 4, 4, ST>(c, a);
+    }
+    if (c->tile_waves == 2) return launch_step_tile<P, 4, 2, ST>(c, a);
+    if (c->tile_rows == 8) return launch_step_tile<P, 8, 1, ST>(c, a);
+    return launch_step_tile<P, 4, 1, ST>(c, a);
+}
+
 template <int P>
 hipError_t launch_step(sclbm_ctx *c, const StepArgs &a) {
-    if constexpr (Prec<P>::DEV) {
-        if (c->tile_waves == 4) return launch_step_tile<P, 4, 4>(c, a);
-    }
-    if (c->tile_waves == 2) return launch_step_tile<P, 4, 2>(c, a);
-    if (c->tile_rows == 8) return launch_step_tile<P, 8, 1>(c, a);
-    return launch_step_tile<P, 4, 1>(c, a);
+    const int w = a.tile_w ? a.tile_w : 64 * c->tile_waves;
+    return cached_stores(c->cfg, w) ? launch_step_st<P, kStoreCached>(c, a) : launch_step_st<P, kStoreNT>(c, a);
 }
 
 hipError_t launch_step_prec(sclbm_ctx *c, const StepArgs &a) {
@@ -551,6 +619,10 @@ sclbm_status sclbm_create(const sclbm_config *cfg, void *dev_workspace, size_t b
     c->par = 0;
     default_tile(*cfg, c->tile_rows, c->tile_waves);
     c->zchunk = default_zchunk(*cfg, c->tile_rows, c->tile_waves);
+    c->def_rows = c->tile_rows;
+    c->def_waves = c->tile_waves;
+    c->def_zc = c->zchunk;
+    default_fit(*cfg, c->fit_w, c->fit_h, c->fit_zc);
     c->tab_first.assign(cfg->nbox, 0);
     c->tab_len.assign(cfg->nbox, 0);
     c->N = int64_t(cfg->nx) * cfg->ny * cfg->nz;
@@ -719,8 +791,11 @@ StepArgs base_args(sclbm_ctx *c) {
     a.nx = c->cfg.nx;
     a.ny = c->cfg.ny;
     a.nz = c->cfg.nz;
-    a.zchunk = c->zchunk;
-    a.nzc = (c->cfg.nz + c->zchunk - 1) / c->zchunk;
+    const bool fit = c->fit_w > 0 && c->tile_rows == c->def_rows && c->tile_waves == c->def_waves && c->zchunk == c->def_zc;
+    a.tile_w = fit ? c->fit_w : 0;
+    a.tile_h = fit ? c->fit_h : 0;
+    a.zchunk = fit ? c->fit_zc : c->zchunk;
+    a.nzc = (c->cfg.nz + a.zchunk - 1) / a.zchunk;
     // tile order: x fastest, then y, then z-chunk (groups of one chunk).  Each XCD
     // then takes a run of neighbouring rows of one chunk, whose ring rows it reads
     // from its own L2.  Groups of up to 4 / (x tiles) chunks had been best or within

@@ -179,23 +179,26 @@ __device__ __forceinline__ float ghost_bracket(const float *A, float dx, float d
 
 #pragma clang fp contract(fast)
 
-template <int P, int TY, int WX, bool GHOST, int WAVES>
-__global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
+template <int P, int TY, int WX, bool GHOST, int WAVES, int ST>
+__global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step_dev(StepArgs a) {
     static_assert(Prec<P>::DEV, "the 16-bit deviation formats");
-    constexpr int TXW = 64 * WX;  // tile width: WX wavefronts per row
-    constexpr int LW = TXW + 2;   // with the ring
+    constexpr bool FIT = TY == 0;     // fitted tile (see k_step)
+    constexpr int NT = step_threads(TY, WX);
+    const int TXW = FIT ? a.tile_w : 64 * WX;  // tile width (fixed: WX wavefronts per row)
+    const int TYR = FIT ? a.tile_h : TY;       // rows
+    const int LW = TXW + 2;                    // row pitch of the LDS arrays
     constexpr uint32_t EB = 4;    // one word (both components) per node and direction
     constexpr int NSLOT = 3;
-    __shared__ float lds[NSLOT][2][TY + 2][LW];
-    __shared__ float4 rmq[NSLOT][TY + 2][LW];  // (m_A, 1 / m_A, m_B, 1 / m_B)
+    __shared__ LdsPlane<float, TY ? TY + 2 : 0, 64 * WX + 2, window_cells(TY, WX)> lds[NSLOT][2];
+    __shared__ LdsPlane<float4, TY ? TY + 2 : 0, 64 * WX + 2, window_cells(TY, WX)> rmq[NSLOT];  // (m_A, 1 / m_A, m_B, 1 / m_B)
     // x exchange: the words with c_x != 0 by slot, row and column lx + 1; columns 0
     // and tw + 1 hold what streams in across the tile's left and right edges
-    __shared__ uint32_t xq[NXD][TY][LW];
+    __shared__ LdsPlane<uint32_t, TY, 64 * WX + 2, exchange_cells(TY, WX)> xq[NXD];
 
-    const int lx = threadIdx.x, ly = threadIdx.y;
-    const int tid = ly * TXW + lx;
-    const int lane = lx & 63;
-    constexpr int NWAVES = TY * WX;
+    const int tid = FIT ? int(threadIdx.x) : int(threadIdx.y) * TXW + int(threadIdx.x);
+    const int ly = FIT ? tid / TXW : int(threadIdx.y), lx = FIT ? tid - ly * TXW : int(threadIdx.x);
+    const int lane = FIT ? tid & 63 : lx & 63;
+    constexpr int NWAVES = NT / 64;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront in the workgroup
     // tile order: as in k_step (contiguous runs per XCD, z-chunks grouped)
     const uint32_t nbx = gridDim.x, nby = gridDim.y;
@@ -212,13 +215,13 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
     t2 /= nby;
     const int chunk = int((t2 % ngr) * zg + ci);
     const int bz = int(t2 / ngr) * a.nzc + chunk;
-    const int x0 = bx * TXW, y0 = by * TY;
+    const int x0 = bx * TXW, y0 = by * TYR;
     const int box = bz / a.nzc;
     const int zs = (bz % a.nzc) * a.zchunk;
     const int ze = min(zs + a.zchunk, a.nz);
     const int x = x0 + lx, y = y0 + ly;
-    const bool valid = (x < a.nx) && (y < a.ny);
-    const int tw = min(TXW, a.nx - x0), th = min(TY, a.ny - y0);
+    const bool valid = (x < a.nx) && (y < a.ny) && (!FIT || ly < TYR);
+    const int tw = min(TXW, a.nx - x0), th = min(TYR, a.ny - y0);
     const bool left_face = x0 == 0, right_face = x0 + tw == a.nx;
     const bool span = left_face && right_face;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
@@ -254,7 +257,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
     const float om0 = uni(float(a.omega[0])), om1 = uni(float(a.omega[1]));
     const float gt0 = uni(float(a.g) * float(a.tau[0])), gt1 = uni(float(a.g) * float(a.tau[1]));
 
-    static_assert(2 * (TXW + 2) + 2 * TY <= TXW * TY, "one ring node per thread");
+    static_assert(FIT || 2 * (64 * WX + 2) + 2 * TY <= NT, "one ring node per thread");  // fitted: fit_ok
     const int ringN = 2 * (tw + 2) + 2 * th;
     const int nplanes = (ze - zs) + 2;
 
@@ -301,14 +304,18 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
     for (int k = 0; k < nplanes; ++k) {
         const int z = zfirst + dir * k;
         const int slot = k % NSLOT;
+        // (fitted tiles: an empty asm keeps what is derived from the pitch in the march; hoisted
+        // out of it, a row address per neighbour row, it spills)
+        int pitch = LW;
+        if constexpr (FIT) asm volatile("" : "+s"(pitch));
         if constexpr (kDebugFill) {
             // debug build: this plane's density slot and the exchange buffer start as NaN
             __syncthreads();
-            lds_fill(&lds[slot][0][0][0], 2 * (TY + 2) * LW, __builtin_nanf(""), tid, 64 * WX * TY);
+            lds_fill(lds[slot][0].data(), 2 * window_cells(TY, WX), __builtin_nanf(""), tid, NT);
             const float qn = __builtin_nanf("");
-            lds_fill(&rmq[slot][0][0], (TY + 2) * LW, make_float4(qn, qn, qn, qn), tid, 64 * WX * TY);
+            lds_fill(rmq[slot].data(), window_cells(TY, WX), make_float4(qn, qn, qn, qn), tid, NT);
             const uint32_t hn = uint32_t(nan_bits<unsigned short>(P));
-            lds_fill(&xq[0][0][0], NXD * TY * LW, hn | (hn << 16), tid, 64 * WX * TY);
+            lds_fill(xq[0].data(), NXD * exchange_cells(TY, WX), hn | (hn << 16), tid, NT);
             __syncthreads();
         }
         // ---- 1. densities of plane z: own node and one ring node per thread ----
@@ -321,10 +328,10 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
         if (valid) {
             const float d0 = own_in ? node_density(fcur, rcur, 0) : rhob[0];
             const float d1 = own_in ? node_density(fcur, rcur, 1) : rhob[1];
-            lds[slot][0][ly + 1][lx + 1] = d0;
-            lds[slot][1][ly + 1][lx + 1] = d1;
+            lds[slot][0].at(pitch, ly + 1, lx + 1) = d0;
+            lds[slot][1].at(pitch, ly + 1, lx + 1) = d1;
             const float2 q0 = dev_ref(d0), q1 = dev_ref(d1);
-            rmq[slot][ly + 1][lx + 1] = make_float4(q0.x, q0.y, q1.x, q1.y);
+            rmq[slot].at(pitch, ly + 1, lx + 1) = make_float4(q0.x, q0.y, q1.x, q1.y);
         }
         if (tid < ringN) {
             // threads 0 .. 2 tw - 1: the ring rows y0 - 1 and y0 + th from x0 (whole
@@ -361,10 +368,10 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
                 rr[0] = node_density(f, rw, 0);
                 rr[1] = node_density(f, rw, 1);
             }
-            lds[slot][0][rsy][rsx] = rr[0];
-            lds[slot][1][rsy][rsx] = rr[1];
+            lds[slot][0].at(pitch, rsy, rsx) = rr[0];
+            lds[slot][1].at(pitch, rsy, rsx) = rr[1];
             const float2 q0 = dev_ref(rr[0]), q1 = dev_ref(rr[1]);
-            rmq[slot][rsy][rsx] = make_float4(q0.x, q0.y, q1.x, q1.y);
+            rmq[slot].at(pitch, rsy, rsx) = make_float4(q0.x, q0.y, q1.x, q1.y);
         }
         __syncthreads();
         // ---- 2. the next plane's loads go out now and land during the collision ----
@@ -381,23 +388,23 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
         const bool zlo = zc == 0, zhi = zc == nz - 1;
         if (valid) {
             const float m[2] = {mval(rprev, 0), mval(rprev, 1)};
-            const float rho[2] = {lds[sl(0)][0][ly + 1][lx + 1], lds[sl(0)][1][ly + 1][lx + 1]};
+            const float rho[2] = {lds[sl(0)][0].at(pitch, ly + 1, lx + 1), lds[sl(0)][1].at(pitch, ly + 1, lx + 1)};
             float sig[2][3], u[2][3];
-            dev_stencil([&](int o, int cx, int cy, int cz) -> float { return lds[sl(cz)][o][ly + 1 + cy][lx + 1 + cx]; },
+            dev_stencil([&](int o, int cx, int cy, int cz) -> float { return lds[sl(cz)][o].at(pitch, ly + 1 + cy, lx + 1 + cx); },
                         sig);
             auto dv = [&](int s, int i) { return dev_of<P>(half_of(fprev[i], s)); };
             dev_shifted(dv, m, rho, sig, om0, om1, gt0, gt1, u);
             // direction i: the two components' values, encoded against the destination's
             // reference densities, as one word
             auto push = [&](int i, float t0, float t1) {
-                const float4 q = rmq[sl(cz_of(i))][ly + 1 + cy_of(i)][lx + 1 + cx_of(i)];
+                const float4 q = rmq[sl(cz_of(i))].at(pitch, ly + 1 + cy_of(i), lx + 1 + cx_of(i));
                 const uint32_t w = uint32_t(dev_enc<P>(t0, q.x, q.y)) | (uint32_t(dev_enc<P>(t1, q.z, q.w)) << 16);
                 if (cx_of(i) != 0) {
-                    xq[xslot_of(i)][ly][lx + 1] = w;
+                    xq[xslot_of(i)].at(pitch, ly, lx + 1) = w;
                     // periodic rows held whole: the wrap across the box's x faces
                     if (!GHOST && span) {
-                        if (cx_of(i) > 0 && lx == tw - 1) xq[xslot_of(i)][ly][0] = w;
-                        if (cx_of(i) < 0 && lx == 0) xq[xslot_of(i)][ly][tw + 1] = w;
+                        if (cx_of(i) > 0 && lx == tw - 1) xq[xslot_of(i)].at(pitch, ly, 0) = w;
+                        if (cx_of(i) < 0 && lx == 0) xq[xslot_of(i)].at(pitch, ly, tw + 1) = w;
                     }
                     return;
                 }
@@ -414,7 +421,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
                     dvo = ((uint32_t(dz) * uint32_t(ny) + uint32_t(dy)) * qnx + uint32_t(x)) * EB +
                           uint32_t(i) * plane_bytes;
                 }
-                __builtin_amdgcn_raw_buffer_store_b32(w, rd, dvo, 0, kStoreNT);
+                __builtin_amdgcn_raw_buffer_store_b32(w, rd, dvo, 0, ST);
             };
             if constexpr (P == SCLBM_BF16DEV) {
                 // BF16 halves are decoded by a shift or a mask, not inside the
@@ -438,7 +445,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
             // the node's reference densities for the next step: its densities now
             const uint32_t rw = uint32_t(__builtin_bit_cast(unsigned short, __float2half_rn(rho[0]))) |
                                 (uint32_t(__builtin_bit_cast(unsigned short, __float2half_rn(rho[1]))) << 16);
-            __builtin_amdgcn_raw_buffer_store_b32(rw, rf_out, 4u * node, 0, kStoreNT);
+            __builtin_amdgcn_raw_buffer_store_b32(rw, rf_out, 4u * node, 0, ST);
         }
         if (GHOST && y < ny) {
             // Populations streaming in from ghost nodes, which hold
@@ -455,7 +462,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
             // lane writes its node's five z directions.
             if (valid && (zlo || zhi)) {
                 const float dx0 = float(x_b) - xcf[0], dy0 = float(y_b) - xcf[1], dz0 = float(zc) - xcf[2];
-                const float4 qr = rmq[sl(0)][ly_b + 1][lx_b + 1];
+                const float4 qr = rmq[sl(0)].at(pitch, ly_b + 1, lx_b + 1);
                 const uint32_t code = zlo ? kZcode[0] : kZcode[1];  // nz >= 3: not both
 #pragma nounroll
                 for (int mz = 0; mz < 5; ++mz) {
@@ -464,7 +471,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
                     const float br = ghost_bracket(A, dx0 - float(cx), dy0 - float(cy), dz0 - float(cz), cx, cy, cz);
                     const uint32_t w = uint32_t(dev_enc<P>(rhob[0] * br, qr.x, qr.y)) |
                                        (uint32_t(dev_enc<P>(rhob[1] * br, qr.z, qr.w)) << 16);
-                    __builtin_amdgcn_raw_buffer_store_b32(w, rd, vo + uint32_t(i) * plane_bytes, 0, kStoreNT);
+                    __builtin_amdgcn_raw_buffer_store_b32(w, rd, vo + uint32_t(i) * plane_bytes, 0, ST);
                 }
             }
         }
@@ -477,13 +484,13 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
             // lane g mod 64, so that few wavefronts issue this code; lane pairs (2m,
             // 2m + 1) share a wavefront, and lane 2m writes the word of both components.
             {
-                constexpr int NXG = 20 * TY, NXW = (NXG + 63) / 64;
-                static_assert(NXW <= NWAVES, "x-face ghosts need more wavefronts than the tile has");
+                const int NXG = 20 * TYR, NXW = (NXG + 63) / 64;
+                static_assert(FIT || (20 * TY + 63) / 64 <= NWAVES, "x-face ghosts need more wavefronts than the tile has");
                 if (wid >= NWAVES - NXW) {
                     int lane_g = lane;
                     asm volatile("" : "+v"(lane_g));
                     const int g = (wid - (NWAVES - NXW)) * 64 + lane_g;
-                    const int side = g / (10 * TY), r = (g / 10) % TY, q = g % 10;
+                    const int side = FIT ? int(g >= 10 * TYR) : g / (10 * TYR), r = FIT ? g / 10 - side * TYR : (g / 10) % TYR, q = g % 10;
                     if (g < NXG && r < th && (side ? right_face : left_face)) {
                         const float *A = gsc, *xcf = gsc + 9;
                         const int sgn = side ? -1 : 1;  // c_x of the incoming directions
@@ -497,11 +504,11 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
                         const float br = ghost_bracket(A, float(fx - sgn) - xcf[0], float(y0 + r) - xcf[1],
                                                        float(zc) - xcf[2], sgn, cyv, czv);
                         // the receiver (fx, y + c_y, z + c_z) lies in the LDS window
-                        const float4 qr = rmq[sl(czv)][r + 1 + cyv][fx - x0 + 1];
+                        const float4 qr = rmq[sl(czv)].at(pitch, r + 1 + cyv, fx - x0 + 1);
                         const uint32_t bits =
                             s ? dev_enc<P>(rhob[1] * br, qr.z, qr.w) : dev_enc<P>(rhob[0] * br, qr.x, qr.y);
                         const uint32_t other = uint32_t(__shfl_xor(int(bits), 1, 64));  // the pair lane's component
-                        if (s == 0) xq[xslot_of(idx)][r][side ? tw + 1 : 0] = bits | (other << 16);
+                        if (s == 0) xq[xslot_of(idx)].at(pitch, r, side ? tw + 1 : 0) = bits | (other << 16);
                     }
                 }
             }
@@ -515,10 +522,11 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
                 int lane_t = lane;
                 asm volatile("" : "+v"(lane_t));
                 const float *A = gsc, *xcf = gsc + 9;
-                // task t: face t / (5 WX), direction (t / WX) mod 5 of its list, column t mod WX
+                // task t: face t / (5 NC), direction (t / NC) mod 5 of its list, column t mod NC
+                const int NC = FIT ? (tw + 63) / 64 : WX;
 #pragma nounroll
-                for (int t = wid; t < 10 * WX; t += NWAVES) {
-                    const int f = t / (5 * WX), my = (t / WX) % 5, c = t % WX;
+                for (int t = wid; t < 10 * NC; t += NWAVES) {
+                    const int f = t / (5 * NC), my = (t / NC) % 5, c = t % NC;
                     if (f ? !fy1 : !fy0) continue;
                     const int i = int(((f ? kYcode[1] : kYcode[0]) >> (5 * my)) & 31u);
                     const int cx = c_rt(0, i), cy = c_rt(1, i), cz = c_rt(2, i);
@@ -527,7 +535,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
                     const int lxn = 64 * c + lane_t, xn = x0 + lxn;
                     // the face node's reference densities (in the window; a column beyond
                     // the tile's nodes reads a cell of the window and stores nothing)
-                    const float4 qr = rmq[sl(0)][yr - y0 + 1][lxn + 1];
+                    const float4 qr = rmq[sl(0)].at(pitch, yr - y0 + 1, lxn + 1);
                     const float br = ghost_bracket(A, (float(xn) - xcf[0]) - float(cx), (float(yr) - xcf[1]) - float(cy),
                                                    (float(zc) - xcf[2]) - float(cz), cx, cy, cz);
                     const uint32_t w = uint32_t(dev_enc<P>(rhob[0] * br, qr.x, qr.y)) |
@@ -535,7 +543,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
                     const uint32_t off = xn < x0 + tw ? ((uint32_t(zc) * uint32_t(ny) + uint32_t(yr)) * qnx +
                                                          uint32_t(i) * uint32_t(nx) + uint32_t(xn)) * EB
                                                       : kOOB;
-                    __builtin_amdgcn_raw_buffer_store_b32(w, rd, off, 0, kStoreNT);
+                    __builtin_amdgcn_raw_buffer_store_b32(w, rd, off, 0, ST);
                 }
             }
         }
@@ -560,15 +568,15 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step_dev(StepArgs a) {
                 bool ok = !out;
                 if (cx > 0 && lx == 0) ok = ok && (GHOST ? left_face : span);
                 if (cx < 0 && lx == tw - 1) ok = ok && (GHOST ? right_face : span);
-                __builtin_amdgcn_raw_buffer_store_b32(xq[jx][ly][lx + 1 - cx], rd, ok ? (row + uint32_t(x)) * EB : kOOB,
-                                                      0, kStoreNT);
+                __builtin_amdgcn_raw_buffer_store_b32(xq[jx].at(pitch, ly, lx + 1 - cx), rd, ok ? (row + uint32_t(x)) * EB : kOOB,
+                                                      0, ST);
                 if (!span) {
                     const bool edge = cx > 0 ? lx == tw - 1 : lx == 0;
                     int xd = x + cx;
                     bool go = edge && !out;
                     if (GHOST) go = go && (cx > 0 ? !right_face : !left_face);
                     else xd = xd < 0 ? xd + nx : (xd >= nx ? xd - nx : xd);
-                    if (go) __builtin_amdgcn_raw_buffer_store_b32(xq[jx][ly][lx + 1], rd, (row + uint32_t(xd)) * EB, 0, kStoreNT);
+                    if (go) __builtin_amdgcn_raw_buffer_store_b32(xq[jx].at(pitch, ly, lx + 1), rd, (row + uint32_t(xd)) * EB, 0, ST);
                 }
             }
         }

@@ -34,7 +34,8 @@
 // wavefront covers 64 aligned consecutive elements, i.e. whole cache lines.
 // (Shifted stores leave partial lines that another wavefront completes later;
 // the same access pattern without arithmetic runs at 3.7 TB/s with shifted
-// stores and 5.1 TB/s with whole-line ones.)  Stores are non-temporal.
+// stores and 5.1 TB/s with whole-line ones.)  Stores are non-temporal where rows start on
+// cache lines, else cached (ST; kStoreNT).
 //
 // Precision.  FP64 storage computes in FP64.  FP32 storage computes the
 // collision in FP32 (or FP64: SCLBM_F32D); the densities of the force
@@ -70,6 +71,7 @@ struct StepArgs {
     int64_t nnode;            // nodes per box
     int nx, ny, nz, nzc, zchunk;
     int zgroup;               // z-chunks that follow one another in the tile order (divides nzc)
+    int tile_w, tile_h;       // fitted tiles (TY = 0): nodes and rows of a tile
     double omega[2];          // 1/tau
     double tau[2];
     double g;                 // G_AB
@@ -195,8 +197,47 @@ __host__ __device__ constexpr uint32_t pack_dirs(const int (&l)[5]) {
 constexpr uint32_t kYcode[2] = {pack_dirs(kYin[0]), pack_dirs(kYin[1])};
 constexpr uint32_t kZcode[2] = {pack_dirs(kZin[0]), pack_dirs(kZin[1])};
 
-template <int P, int TY, int WX, bool GHOST, int WAVES>
-__global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
+// Threads of a step workgroup: TY rows of WX wavefronts, or WX wavefronts for a fitted tile (TY = 0).
+__host__ __device__ constexpr int step_threads(int ty, int wx) { return 64 * wx * (ty == 0 ? 1 : ty); }
+// Fitted tiles.  A tile of fixed width leaves the lanes beyond the row's end idle (100 nodes: 28 of
+// 128 lanes; 70 nodes: 58), and in registers and issue slots they cost what the others do.  A fitted tile
+// takes its width from the row (the whole row, or an equal part of it) and as many rows as its
+// threads hold, thread t at node t mod width of row t / width.
+constexpr int FIT_ROWS = 24;  // most rows (the x-face ghosts of a tile are one entry per thread)
+constexpr int FIT_WIDTH = 128;  // widest
+constexpr int FIT_WAVES = 8;    // wavefronts
+// LDS cells per plane: the density window with its ring, and the x exchange.  For a fitted tile of
+// w x h nodes (w h <= threads): (w + 2) (h + 2) and (w + 2) h at most.
+__host__ __device__ constexpr int window_cells(int ty, int wx) {
+    return ty ? (ty + 2) * (64 * wx + 2) : 64 * wx + 2 * FIT_ROWS + 2 * FIT_WIDTH + 4;
+}
+__host__ __device__ constexpr int exchange_cells(int ty, int wx) {
+    return ty ? ty * (64 * wx + 2) : 64 * wx + 2 * FIT_ROWS;
+}
+// One plane of an LDS array: R rows of C cells, or (R = 0) N cells addressed with the tile's own row pitch.
+template <typename T, int R, int C, int N>
+struct LdsPlane {
+    static_assert(R * C == N, "cells");
+    T v[R][C];
+    __device__ __forceinline__ T &at(int, int r, int c) { return v[r][c]; }
+    __device__ __forceinline__ T *data() { return &v[0][0]; }
+};
+template <typename T, int C, int N>
+struct LdsPlane<T, 0, C, N> {
+    T v[N];
+    __device__ __forceinline__ T &at(int pitch, int r, int c) { return v[r * pitch + c]; }
+    __device__ __forceinline__ T *data() { return v; }
+};
+// Whether FIT_WAVES wavefronts can run tiles of w x h nodes: the node, ring (one node a thread) and ghost
+// counts the kernels assume.  The y-face tasks read window cells up to column 64 ceil(w / 64).
+__host__ __device__ constexpr bool fit_ok(int w, int h) {
+    return w >= 3 && h >= 1 && h <= FIT_ROWS && w <= FIT_WIDTH && w * h <= 64 * FIT_WAVES &&
+           2 * (w + 2) + 2 * h <= 64 * FIT_WAVES && 20 * h <= 64 * FIT_WAVES &&
+           h * (w + 2) + (w + 63) / 64 * 64 < window_cells(0, FIT_WAVES);
+}
+
+template <int P, int TY, int WX, bool GHOST, int WAVES, int ST>
+__global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a) {
     using S = typename Prec<P>::S;
     using W = typename Prec<P>::W;
     using R = typename Prec<P>::R;
@@ -204,8 +245,11 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
     using L = typename Prec<P>::L;
     using C = R;  // collision arithmetic
     using D = typename Prec<P>::D;  // densities of the force stencil
-    constexpr int TXW = 64 * WX;  // tile width: WX wavefronts per row
-    constexpr int LW = TXW + 2;   // with the ring
+    constexpr bool FIT = TY == 0;     // fitted tile: width and rows from the launch
+    constexpr int NT = step_threads(TY, WX);
+    const int TXW = FIT ? a.tile_w : 64 * WX;  // tile width (fixed: WX wavefronts per row)
+    const int TYR = FIT ? a.tile_h : TY;       // rows
+    const int LW = TXW + 2;                    // row pitch of the LDS arrays: the width with the ring
     constexpr uint32_t EB = sizeof(S);
     // the next plane's populations (raw words, decoded when the plane is used, so
     // that nothing waits for them during the collision) are loaded while the
@@ -216,17 +260,17 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
     static_assert(!Prec<P>::DEV, "the 16-bit deviation formats run k_step_dev");
     // density window: the planes zc - 1, zc, zc + 1 of the collision and one more
     constexpr int NSLOT = 4;
-    __shared__ D lds[NSLOT][2][TY + 2][LW];
+    __shared__ LdsPlane<D, TY ? TY + 2 : 0, 64 * WX + 2, window_cells(TY, WX)> lds[NSLOT][2];
     // x exchange: post-collision values with c_x != 0, by component, slot, row and
     // column lx + 1; columns 0 and tw + 1 hold what streams in across the tile's
     // left and right edges (ghost populations, or the periodic wrap)
-    __shared__ B xq[2][NXD][TY][LW];
+    __shared__ LdsPlane<B, TY, 64 * WX + 2, exchange_cells(TY, WX)> xq[2][NXD];
 
-    const int lx = threadIdx.x, ly = threadIdx.y;
-    const int tid = ly * TXW + lx;
-    const int lane = lx & 63;
+    const int tid = FIT ? int(threadIdx.x) : int(threadIdx.y) * TXW + int(threadIdx.x);
+    const int ly = FIT ? tid / TXW : int(threadIdx.y), lx = FIT ? tid - ly * TXW : int(threadIdx.x);
+    const int lane = FIT ? tid & 63 : lx & 63;
     // wavefront index within the workgroup, uniform (a scalar register)
-    constexpr int NWAVES = TY * WX;
+    constexpr int NWAVES = NT / 64;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     // XCD-aware tile order: workgroups are dispatched round-robin over the 8
     // XCDs by linear id, so give XCD k one contiguous run of tiles, ordered x
@@ -251,13 +295,13 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
     t2 /= nby;
     const int chunk = int((t2 % ngr) * zg + ci);
     const int bz = int(t2 / ngr) * a.nzc + chunk;
-    const int x0 = bx * TXW, y0 = by * TY;
+    const int x0 = bx * TXW, y0 = by * TYR;
     const int box = bz / a.nzc;
     const int zs = (bz % a.nzc) * a.zchunk;
     const int ze = min(zs + a.zchunk, a.nz);
     const int x = x0 + lx, y = y0 + ly;
-    const bool valid = (x < a.nx) && (y < a.ny);
-    const int tw = min(TXW, a.nx - x0), th = min(TY, a.ny - y0);  // valid tile extent
+    const bool valid = (x < a.nx) && (y < a.ny) && (!FIT || ly < TYR);
+    const int tw = min(TXW, a.nx - x0), th = min(TYR, a.ny - y0);  // valid tile extent
     const bool left_face = x0 == 0, right_face = x0 + tw == a.nx;
     const bool span = left_face && right_face;                     // the tile holds whole rows
     const int nx = a.nx, ny = a.ny, nz = a.nz;
@@ -287,7 +331,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
         for (int q = 0; q < 9; ++q) Am[q] = R(Arow[q]);
     }
 
-    static_assert(2 * (TXW + 2) + 2 * TY <= TXW * TY, "one ring node per thread");
+    static_assert(FIT || 2 * (64 * WX + 2) + 2 * TY <= NT, "one ring node per thread");  // fitted: fit_ok
     const int ringN = 2 * (tw + 2) + 2 * th;
     const int nplanes = (ze - zs) + 2;
 
@@ -336,11 +380,15 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
     for (int k = 0; k < nplanes; ++k) {
         const int z = zfirst + dir * k;
         const int slot = k % NSLOT;
+        // (fitted tiles: an empty asm keeps what is derived from the pitch in the march; hoisted
+        // out of it, a row address per neighbour row, it spills)
+        int pitch = LW;
+        if constexpr (FIT) asm volatile("" : "+s"(pitch));
         if constexpr (kDebugFill) {
             // debug build: this plane's density slot and the exchange buffer start as NaN
             __syncthreads();
-            lds_fill(&lds[slot][0][0][0], 2 * (TY + 2) * LW, D(__builtin_nan("")), tid, 64 * WX * TY);
-            lds_fill(&xq[0][0][0][0], 2 * NXD * TY * LW, nan_bits<B>(P), tid, 64 * WX * TY);
+            lds_fill(lds[slot][0].data(), 2 * window_cells(TY, WX), D(__builtin_nan("")), tid, NT);
+            lds_fill(xq[0][0].data(), 2 * NXD * exchange_cells(TY, WX), nan_bits<B>(P), tid, NT);
             __syncthreads();
         }
         // ---- 1. densities of plane z: own node (into the register window) and one
@@ -395,8 +443,8 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
         if (valid) {
             const D r0 = own_in ? pair_density<D>(fcur[0]) : rhobd[0];
             const D r1 = own_in ? pair_density<D>(fcur[1]) : rhobd[1];
-            lds[slot][0][ly + 1][lx + 1] = r0;
-            lds[slot][1][ly + 1][lx + 1] = r1;
+            lds[slot][0].at(pitch, ly + 1, lx + 1) = r0;
+            lds[slot][1].at(pitch, ly + 1, lx + 1) = r1;
         }
         if (ring_on) {
             D rr[2] = {rhobd[0], rhobd[1]};
@@ -409,8 +457,8 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
                     rr[s] = pair_density<D>(f);
                 }
             }
-            lds[slot][0][rsy][rsx] = rr[0];
-            lds[slot][1][rsy][rsx] = rr[1];
+            lds[slot][0].at(pitch, rsy, rsx) = rr[0];
+            lds[slot][1].at(pitch, rsy, rsx) = rr[1];
         }
         __syncthreads();
         // ---- 2. the next plane's loads go out now and land during the collision ----
@@ -434,7 +482,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
 #pragma unroll
                 for (int p = 1; p <= 9; ++p) d[p] = R(f[s][2 * p - 1]) - R(f[s][2 * p]);
                 // the density summed when the plane was loaded (same value)
-                rho[s] = R(lds[sl(0)][s][ly + 1][lx + 1]);
+                rho[s] = R(lds[sl(0)][s].at(pitch, ly + 1, lx + 1));
                 j[s][0] = d[1] + d[4] + d[5] + d[6] + d[7];
                 j[s][1] = d[2] + d[4] - d[5] + d[8] + d[9];
                 j[s][2] = d[3] + d[6] - d[7] + d[8] - d[9];
@@ -449,8 +497,8 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
 #pragma unroll
                 for (int p = 1; p <= 9; ++p) {
                     const int i = 2 * p - 1;
-                    const D hi = lds[sl(cz_of(i))][o][ly + 1 + cy_of(i)][lx + 1 + cx_of(i)];
-                    const D lo = lds[sl(-cz_of(i))][o][ly + 1 - cy_of(i)][lx + 1 - cx_of(i)];
+                    const D hi = lds[sl(cz_of(i))][o].at(pitch, ly + 1 + cy_of(i), lx + 1 + cx_of(i));
+                    const D lo = lds[sl(-cz_of(i))][o].at(pitch, ly + 1 - cy_of(i), lx + 1 - cx_of(i));
                     e[p] = hi - lo;
                 }
                 const D w1 = D(1) / D(18), w2 = D(1) / D(36);
@@ -498,11 +546,11 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
                     }
                     const B bits = Prec<P>::enc(pst, C(0));
                     if (cx_of(i) != 0) {
-                        xq[s][xslot_of(i)][ly][lx + 1] = bits;
+                        xq[s][xslot_of(i)].at(pitch, ly, lx + 1) = bits;
                         // periodic rows held whole: the wrap across the box's x faces
                         if (!GHOST && span) {
-                            if (cx_of(i) > 0 && lx == tw - 1) xq[s][xslot_of(i)][ly][0] = bits;
-                            if (cx_of(i) < 0 && lx == 0) xq[s][xslot_of(i)][ly][tw + 1] = bits;
+                            if (cx_of(i) > 0 && lx == tw - 1) xq[s][xslot_of(i)].at(pitch, ly, 0) = bits;
+                            if (cx_of(i) < 0 && lx == 0) xq[s][xslot_of(i)].at(pitch, ly, tw + 1) = bits;
                         }
                         return;
                     }
@@ -519,7 +567,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
                         dvo = ((uint32_t(dz) * uint32_t(ny) + uint32_t(dy)) * qnx + uint32_t(x)) * EB +
                               uint32_t(i) * plane_bytes;
                     }
-                    Prec<P>::bstore_bits(rd[s], dvo, 0, bits);
+                    Prec<P>::template bstore_bits<ST>(rd[s], dvo, 0, bits);
                 };
                 equilibrium_pairs<C>(ux, uy, uz, r, aa, r3, r45, push);
             }
@@ -554,7 +602,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
                     const R wgt = i < 7 ? R(1) / R(18) : R(1) / R(36);
 #pragma unroll
                     for (int s = 0; s < 2; ++s)
-                        Prec<P>::bstore_bits(rd[s], vo + uint32_t(i) * plane_bytes, 0, Prec<P>::enc(wgt * rhob[s] * br, R(0)));
+                        Prec<P>::template bstore_bits<ST>(rd[s], vo + uint32_t(i) * plane_bytes, 0, Prec<P>::enc(wgt * rhob[s] * br, R(0)));
                 }
             }
         }
@@ -566,11 +614,11 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
             // the tile's last wavefronts, entry g = (side TY + row) 10 + 2m + s in
             // lane g mod 64, so that few wavefronts issue this code.
             {
-                constexpr int NXG = 20 * TY, NXW = (NXG + 63) / 64;
-                static_assert(NXW <= NWAVES, "x-face ghosts need more wavefronts than the tile has");
+                const int NXG = 20 * TYR, NXW = (NXG + 63) / 64;
+                static_assert(FIT || (20 * TY + 63) / 64 <= NWAVES, "x-face ghosts need more wavefronts than the tile has");
                 if (wid >= NWAVES - NXW) {
                     const int g = (wid - (NWAVES - NXW)) * 64 + lane;
-                    const int side = g / (10 * TY), r = (g / 10) % TY, q = g % 10;
+                    const int side = FIT ? int(g >= 10 * TYR) : g / (10 * TYR), r = FIT ? g / 10 - side * TYR : (g / 10) % TYR, q = g % 10;
                     if (g < NXG && r < th && (side ? right_face : left_face)) {
                         const int sgn = side ? -1 : 1;  // c_x of the incoming directions
                         const int m = q >> 1, s = q & 1;
@@ -590,7 +638,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
                         const R geq =
                             wgt * (s ? rhob[1] : rhob[0]) * (R(1) + R(3) * cu + R(4.5) * cu * cu - R(1.5) * usq);
                         // the receiver (fx, y + c_y, z + c_z) lies in the LDS window (plane slots k-2..k)
-                        xq[s][xslot_of(idx)][r][side ? tw + 1 : 0] = Prec<P>::enc(geq, R(0));
+                        xq[s][xslot_of(idx)].at(pitch, r, side ? tw + 1 : 0) = Prec<P>::enc(geq, R(0));
                     }
                 }
             }
@@ -601,10 +649,11 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
             // not hold up the tile's barrier.
             const bool fy0 = y0 == 0, fy1 = y0 + th == ny;
             if (fy0 || fy1) {
-                // task t: face t / (5 WX), direction (t / WX) mod 5 of its list, column t mod WX
+                // task t: face t / (5 NC), direction (t / NC) mod 5 of its list, column t mod NC
+                const int NC = FIT ? (tw + 63) / 64 : WX;
 #pragma nounroll
-                for (int t = wid; t < 10 * WX; t += NWAVES) {
-                    const int f = t / (5 * WX), m = (t / WX) % 5, c = t % WX;
+                for (int t = wid; t < 10 * NC; t += NWAVES) {
+                    const int f = t / (5 * NC), m = (t / NC) % 5, c = t % NC;
                     if (f ? !fy1 : !fy0) continue;
                     const int i = int(((f ? kYcode[1] : kYcode[0]) >> (5 * m)) & 31u);
                     const int cz = c_rt(2, i);
@@ -618,7 +667,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
                     const R wgt = i < 7 ? R(1) / R(18) : R(1) / R(36);
 #pragma unroll
                     for (int s = 0; s < 2; ++s)
-                        Prec<P>::bstore_bits(rd[s], off, 0, Prec<P>::enc(wgt * rhob[s] * br, R(0)));
+                        Prec<P>::template bstore_bits<ST>(rd[s], off, 0, Prec<P>::enc(wgt * rhob[s] * br, R(0)));
                 }
             }
         }
@@ -635,7 +684,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
             for (int jx = 0; jx < NXD; ++jx) {
                 const int cx = cx_of(jx < 2 ? jx + 1 : jx + 5);
 #pragma unroll
-                for (int s = 0; s < 2; ++s) wq[s][jx] = xq[s][jx][ly][lx + 1 - cx];
+                for (int s = 0; s < 2; ++s) wq[s][jx] = xq[s][jx].at(pitch, ly, lx + 1 - cx);
             }
             // destination row of direction i and whether it lies outside the box (ghost mode)
             auto dest_row = [&](int i, bool &out) -> uint32_t {
@@ -659,7 +708,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
                 if (cx > 0 && lx == 0) ok = ok && (GHOST ? left_face : span);
                 if (cx < 0 && lx == tw - 1) ok = ok && (GHOST ? right_face : span);
 #pragma unroll
-                for (int s = 0; s < 2; ++s) Prec<P>::bstore_bits(rd[s], ok ? (row + uint32_t(x)) * EB : kOOB, 0, wq[s][jx]);
+                for (int s = 0; s < 2; ++s) Prec<P>::template bstore_bits<ST>(rd[s], ok ? (row + uint32_t(x)) * EB : kOOB, 0, wq[s][jx]);
             }
             // a tile that does not hold whole rows also writes the value leaving it
             // across each edge, in a loop of its own so that no branch separates the
@@ -679,7 +728,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
                     if (go) {
 #pragma unroll
                         for (int s = 0; s < 2; ++s)
-                            Prec<P>::bstore_bits(rd[s], (row + uint32_t(xd)) * EB, 0, xq[s][jx][ly][lx + 1]);
+                            Prec<P>::template bstore_bits<ST>(rd[s], (row + uint32_t(xd)) * EB, 0, xq[s][jx].at(pitch, ly, lx + 1));
                     }
                 }
             }
@@ -703,7 +752,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
                 if (cx < 0 && lx == tw - 1) ok = ok && (GHOST ? right_face : span);
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
-                    Prec<P>::bstore_bits(rd[s], ok ? (row + uint32_t(x)) * EB : kOOB, 0, xq[s][jx][ly][lx + 1 - cx]);
+                    Prec<P>::template bstore_bits<ST>(rd[s], ok ? (row + uint32_t(x)) * EB : kOOB, 0, xq[s][jx].at(pitch, ly, lx + 1 - cx));
                 if (!span) {
                     const bool edge = cx > 0 ? lx == tw - 1 : lx == 0;
                     int xd = x + cx;
@@ -713,7 +762,7 @@ __global__ __launch_bounds__(64 * WX * TY, WAVES) void k_step(StepArgs a) {
                     if (go) {
 #pragma unroll
                         for (int s = 0; s < 2; ++s)
-                            Prec<P>::bstore_bits(rd[s], (row + uint32_t(xd)) * EB, 0, xq[s][jx][ly][lx + 1]);
+                            Prec<P>::template bstore_bits<ST>(rd[s], (row + uint32_t(xd)) * EB, 0, xq[s][jx].at(pitch, ly, lx + 1));
                     }
                 }
             }

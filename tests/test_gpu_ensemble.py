@@ -200,3 +200,36 @@ def test_moments_of_all_boxes_in_one_pass(sc):
         ra, rb, _ = (t.cpu().numpy() for t in lat.fields(box=b))
         ref = oracle.droplet_moments(ra, rb, lat.xc)
         assert np.allclose(allm[b].cpu().numpy(), ref, rtol=1e-12, atol=1e-9)
+
+
+@pytest.mark.parametrize("bc", ["ghost", "periodic"])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16dev", "bf16dev"])
+@pytest.mark.parametrize("nxyz,nbox", [((21, 89, 20), 3), ((20, 130, 22), 4), ((150, 40, 30), 1), ((130, 61, 30), 1),
+                                       ((260, 31, 30), 1), ((97, 60, 33), 2), ((100, 120, 90), 1)])
+def test_fitted_tiles_equal_fixed_tiles(sc, nxyz, nbox, prec, bc):
+    """Boxes whose default launch takes tiles fitted to the row (whole rows of 20 to
+    100 nodes, the row count at its limit of 24, rows cut into two to four parts with a
+    narrower last one, a last tile of fewer rows) against 64 x 4 tiles in chunks
+    of three planes: the states of every box are the same bytes after seven steps, and the
+    cached stores that rows off the cache lines take write the same as the streaming
+    ones (100-node FP64 rows)."""
+    nx, ny, nz = nxyz
+    lats = [sc.Lattice(nx, ny, nz, nbox=nbox, bc=bc, prec=prec, table_len=8, tau=(1.0, 1.2), g_ab=wl.G_AB,
+                       rho_b=wl.ghost_densities(8.0)) for _ in range(2)]
+    rng = np.random.default_rng(nx)
+    for b in range(nbox):
+        ctr = np.array([nx, ny, nz]) / 2.0 + rng.uniform(-2, 2, 3)
+        A = 1e-3 * rng.standard_normal(9)
+        A[8] = -A[0] - A[4]
+        tab = np.array([A * (1 + 0.1 * t) for t in range(8)])
+        for lat in lats:
+            lat.init_droplet(ctr, 0.3 * min(nxyz), wl.WIDTH, wl.RHO_HI, wl.RHO_LO, A if bc == "ghost" else None, box=b)
+            if bc == "ghost":
+                lat.set_gradient_table(tab, 0, box=b)
+    lats[1].set_launch(4, 3, 1)
+    for lat in lats:
+        lat.step(7)
+    a, b = (lat.save() for lat in lats)
+    assert np.array_equal(a, b)
+    ra, rb = (t.cpu().numpy() for t in lats[0].fields(box=nbox - 1, velocity=False))
+    assert np.isfinite(ra).all() and np.isfinite(rb).all()
