@@ -146,6 +146,11 @@ sclbm_status scratch_address(int dev, double **out) {
 
 }  // namespace
 
+// Workgroups that hold several planes at once: planes, wavefronts per plane (planes = 0: none).
+struct SmallShape {
+    int planes = 0, waves = 0;
+};
+
 struct sclbm_ctx {
     sclbm_config cfg;
     Layout lay;
@@ -157,6 +162,7 @@ struct sclbm_ctx {
     int tile_waves;   // WX: wavefronts per tile row (tile width 64 WX)
     int zchunk;
     int def_rows = 0, def_waves = 0, def_zc = 0;  // the default launch shape
+    SmallShape small;                             // ... as chunks of one or two planes at once (planes = 0: not)
     int fit_w = 0, fit_h = 0, fit_zc = 0;         // fitted tiles that run in its place (0: none)
     std::vector<int64_t> tab_first, tab_len;  // host copies, per box
     // captured step loop: valid for (graph_steps, graph_par, graph_ty, graph_wx, graph_zc)
@@ -304,7 +310,7 @@ void default_fit(const sclbm_config &c, int &w, int &h, int &zc) {
     for (int ntx = 1; ntx <= 8; ++ntx) {
         const int fw = (c.nx + ntx - 1) / ntx;
         int fh = std::min(64 * FIT_WAVES / fw, FIT_ROWS);
-        while (fh > 0 && !fit_ok(fw, fh)) --fh;
+        while (fh > 0 && !fit_ok(fw, fh, FIT_WAVES)) --fh;
         if (fh < 1) continue;
         const long tiles = long((c.nx + fw - 1) / fw) * long((c.ny + fh - 1) / fh) * c.nbox;
         const int z = best_zchunk(c, tiles, resident_groups(c, FIT_WAVES), cost);
@@ -314,6 +320,38 @@ void default_fit(const sclbm_config &c, int &w, int &h, int &zc) {
         h = fh;
         zc = z;
     }
+}
+
+// Small boxes.  A march needs its planes one after the other, each with a load's latency and a
+// barrier or two, and a box of few tiles leaves CUs idle however its chunks are cut: 16 us per step
+// is the least that any box takes so.  There all planes of a chunk of one or two are loaded at once, each by
+// wavefronts of its own (k_step's PL), and nothing is left to wait for in turn.  It reads every population
+// three times (one plane a chunk) or twice instead of once, from the caches, so it pays while one
+// workgroup per CU holds the whole of the boxes: the fewest planes and wavefronts for which that is so, the fewest
+// tiles in a row, then the fewest rows.  Measured, us per step, march -> planes at once:
+// 32^3 FP64 22.2 -> 8.9, FP32 16.7 -> 8.5, FP16 16.4 -> 6.9 (256 workgroups of 3 x 2 wavefronts; of 4 x 2, 128
+// of them, 9.9, 8.8, 7.3); 45 x 33 x 29 FP32 22.2 -> 9.2 (255 of 4 x 2); 40 x 57 x 33 FP64 31.4 -> 15.0
+// (255 of 4 x 3), 48^3 FP32 18.3 -> 12.2 (240 of 4 x 4).  Above that line the march: 64^3 FP32 20.4, at once
+// 23.4 (512 of 4 x 4); FP64 48^3 27.2 and 25.2 (288).
+// wavefronts per plane of the largest workgroup: four planes of four leave a thread 128 registers, which FP64
+// arithmetic exceeds
+constexpr int widest_small(int prec) { return prec == SCLBM_F64 || prec == SCLBM_F32D ? 3 : 4; }
+SmallShape small_tiles(const sclbm_config &c, int &w, int &h) {
+    const SmallShape shapes[] = {{3, 2}, {4, 2}, {4, widest_small(c.prec)}};
+    for (const SmallShape &s : shapes) {
+        const long layers = (long(c.nz) + s.planes - 3) / (s.planes - 2) * c.nbox;
+        for (int ntx = 1; ntx <= 4; ++ntx) {
+            const int fw = (c.nx + ntx - 1) / ntx;
+            for (int fh = 1; fit_ok(fw, fh, s.waves); ++fh) {
+                if (long((c.nx + fw - 1) / fw) * ((c.ny + fh - 1) / fh) * layers > 256) continue;
+                w = fw;
+                h = fh;
+                return s;
+            }
+        }
+    }
+    w = h = 0;
+    return SmallShape{};
 }
 
 // Store policy of a launch with tiles w nodes wide: cached where the rows' runs of one direction
@@ -357,9 +395,38 @@ hipError_t launch_step_tile(sclbm_ctx *c, const StepArgs &a) {
     return hipGetLastError();
 }
 
+// ... in chunks of PL - 2 planes, every plane of the density window on WX wavefronts of its own.
+// Streaming stores for all rows: FP64 32^3 8.9 us per step, with cached ones 10.4; FP32 40 x 57 x 33 11.1, 12.6.
+template <int P, int PL, int WX>
+hipError_t launch_step_planes(sclbm_ctx *c, const StepArgs &a) {
+    const dim3 block(64 * WX, PL, 1);
+    const dim3 grid((c->cfg.nx + a.tile_w - 1) / a.tile_w, (c->cfg.ny + a.tile_h - 1) / a.tile_h, a.nzc * c->cfg.nbox);
+    constexpr int WAVES = (PL * WX + 3) / 4;  // per SIMD: one workgroup per CU
+    if constexpr (Prec<P>::DEV) {
+        if (c->cfg.bc == SCLBM_BC_GHOST)
+            hipLaunchKernelGGL((k_step_dev<P, 0, WX, true, WAVES, kStoreNT, PL>), grid, block, 0, c->stream, a);
+        else
+            hipLaunchKernelGGL((k_step_dev<P, 0, WX, false, WAVES, kStoreNT, PL>), grid, block, 0, c->stream, a);
+    } else {
+        if (c->cfg.bc == SCLBM_BC_GHOST)
+            hipLaunchKernelGGL((k_step<P, 0, WX, true, WAVES, kStoreNT, PL>), grid, block, 0, c->stream, a);
+        else
+            hipLaunchKernelGGL((k_step<P, 0, WX, false, WAVES, kStoreNT, PL>), grid, block, 0, c->stream, a);
+    }
+    return hipGetLastError();
+}
+template <int P>
+hipError_t launch_step_small(sclbm_ctx *c, const StepArgs &a) {
+    if (c->small.planes == 3) return launch_step_planes<P, 3, 2>(c, a);
+    if (c->small.waves == 2) return launch_step_planes<P, 4, 2>(c, a);
+    return launch_step_planes<P, 4, widest_small(P)>(c, a);
+}
+
 template <int P, int ST>
 hipError_t launch_step_st(sclbm_ctx *c, const StepArgs &a) {
-    if (a.tile_w) return launch_step_tile<P, 0, FIT_WAVES, ST>(c, a);
+    if constexpr (P != SCLBM_F32D) {  // (no fitted march: default_fit)
+        if (a.tile_w) return launch_step_tile<P, 0, FIT_WAVES, ST>(c, a);
+    }
     if constexpr (Prec<P>::DEV) {
         if (c->tile_waves == 4) return launch_step_tile<P, 4, 4, ST>(c, a);
     }
@@ -370,6 +437,7 @@ hipError_t launch_step_st(sclbm_ctx *c, const StepArgs &a) {
 
 template <int P>
 hipError_t launch_step(sclbm_ctx *c, const StepArgs &a) {
+    if (a.tile_w && c->small.planes) return launch_step_small<P>(c, a);
     const int w = a.tile_w ? a.tile_w : 64 * c->tile_waves;
     return cached_stores(c->cfg, w) ? launch_step_st<P, kStoreCached>(c, a) : launch_step_st<P, kStoreNT>(c, a);
 }
@@ -622,7 +690,9 @@ sclbm_status sclbm_create(const sclbm_config *cfg, void *dev_workspace, size_t b
     c->def_rows = c->tile_rows;
     c->def_waves = c->tile_waves;
     c->def_zc = c->zchunk;
-    default_fit(*cfg, c->fit_w, c->fit_h, c->fit_zc);
+    c->small = small_tiles(*cfg, c->fit_w, c->fit_h);
+    c->fit_zc = c->small.planes - 2;
+    if (!c->small.planes) default_fit(*cfg, c->fit_w, c->fit_h, c->fit_zc);
     c->tab_first.assign(cfg->nbox, 0);
     c->tab_len.assign(cfg->nbox, 0);
     c->N = int64_t(cfg->nx) * cfg->ny * cfg->nz;

@@ -179,8 +179,8 @@ __device__ __forceinline__ float ghost_bracket(const float *A, float dx, float d
 
 #pragma clang fp contract(fast)
 
-template <int P, int TY, int WX, bool GHOST, int WAVES, int ST>
-__global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step_dev(StepArgs a) {
+template <int P, int TY, int WX, bool GHOST, int WAVES, int ST, int PL = 0>
+__global__ __launch_bounds__(step_threads(TY, WX) * (PL ? PL : 1), WAVES) void k_step_dev(StepArgs a) {
     static_assert(Prec<P>::DEV, "the 16-bit deviation formats");
     constexpr bool FIT = TY == 0;     // fitted tile (see k_step)
     constexpr int NT = step_threads(TY, WX);
@@ -188,12 +188,17 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step_dev(StepAr
     const int TYR = FIT ? a.tile_h : TY;       // rows
     const int LW = TXW + 2;                    // row pitch of the LDS arrays
     constexpr uint32_t EB = 4;    // one word (both components) per node and direction
-    constexpr int NSLOT = 3;
+    constexpr int NSLOT = PL ? PL : 3;
+    // PL planes at once (see k_step)
+    static_assert(PL == 0 || (FIT && (PL == 3 || PL == 4)), "chunks of one or two planes, fitted tiles");
+    const int plane = PL ? int(threadIdx.y) : 0;
+    const int pair = PL == 4 ? plane >> 1 : 0;
     __shared__ LdsPlane<float, TY ? TY + 2 : 0, 64 * WX + 2, window_cells(TY, WX)> lds[NSLOT][2];
     __shared__ LdsPlane<float4, TY ? TY + 2 : 0, 64 * WX + 2, window_cells(TY, WX)> rmq[NSLOT];  // (m_A, 1 / m_A, m_B, 1 / m_B)
     // x exchange: the words with c_x != 0 by slot, row and column lx + 1; columns 0
     // and tw + 1 hold what streams in across the tile's left and right edges
-    __shared__ LdsPlane<uint32_t, TY, 64 * WX + 2, exchange_cells(TY, WX)> xq[NXD];
+    __shared__ LdsPlane<uint32_t, TY, 64 * WX + 2, exchange_cells(TY, WX)> xqs[PL == 4 ? 2 : 1][NXD];
+    auto &xq = xqs[pair];
 
     const int tid = FIT ? int(threadIdx.x) : int(threadIdx.y) * TXW + int(threadIdx.x);
     const int ly = FIT ? tid / TXW : int(threadIdx.y), lx = FIT ? tid - ly * TXW : int(threadIdx.x);
@@ -219,11 +224,18 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step_dev(StepAr
     const int box = bz / a.nzc;
     const int zs = (bz % a.nzc) * a.zchunk;
     const int ze = min(zs + a.zchunk, a.nz);
+    const bool here = PL == 0 || zs + pair < ze;  // (the last chunk of an odd count of planes has one)
+    const bool collides = PL == 0 || (here && (plane == 1 || (PL == 4 && plane == 2)));
+    const bool xy_ghosts = PL == 0 || (here && (plane == 0 || (PL == 4 && plane == 3)));
+    const bool z_ghosts = PL == 0 || (here && (PL == 3 ? plane == 2 : (plane == 0 || plane == 3)));
+    const bool stores = PL == 0 || (here && !(PL == 3 && plane == 1));
+    const int half = PL == 3 ? plane >> 1 : plane & 1;  // which half of the stores
     const int x = x0 + lx, y = y0 + ly;
     const bool valid = (x < a.nx) && (y < a.ny) && (!FIT || ly < TYR);
     const int tw = min(TXW, a.nx - x0), th = min(TYR, a.ny - y0);
     const bool left_face = x0 == 0, right_face = x0 + tw == a.nx;
     const bool span = left_face && right_face;
+    const bool wrap_lo = span && lx == 0, wrap_hi = span && lx == tw - 1;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const uint32_t N = uint32_t(a.nnode);
     const uint32_t nxy = uint32_t(nx) * uint32_t(ny);
@@ -298,12 +310,12 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step_dev(StepAr
     };
     const int dir = (chunk & 1) ? -1 : 1;
     const int zfirst = dir > 0 ? zs - 1 : ze;
-    prefetch(zfirst);
+    prefetch(PL ? zs - 1 + plane : zfirst);
 
     uint32_t fprev[Q], fcur[Q], rprev = 0u, rcur = 0u;
-    for (int k = 0; k < nplanes; ++k) {
-        const int z = zfirst + dir * k;
-        const int slot = k % NSLOT;
+    for (int k = PL ? 2 : 0; k < (PL ? 3 : nplanes); ++k) {
+        const int z = PL ? zs - 1 + plane : zfirst + dir * k;
+        const int slot = PL ? plane : k % NSLOT;
         // (fitted tiles: an empty asm keeps what is derived from the pitch in the march; hoisted
         // out of it, a row address per neighbour row, it spills)
         int pitch = LW;
@@ -375,18 +387,23 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step_dev(StepAr
         }
         __syncthreads();
         // ---- 2. the next plane's loads go out now and land during the collision ----
-        if (k + 1 < nplanes) prefetch(z + dir);
+        if (PL == 0 && k + 1 < nplanes) prefetch(z + dir);
         if (k >= 2) {
         // ---- 3. collide plane zc = z - dir: c_x = 0 words are pushed now, the others
         // go through LDS ----
-        const int zc = z - dir;
-        auto sl = [&](int d) { return (k - 1 + dir * d) % NSLOT; };  // k >= 2: never negative
+        const int zc = PL ? zs + pair : z - dir;
+        auto sl = [&](int d) { return PL ? pair + 1 + d : (k - 1 + dir * d) % NSLOT; };  // k >= 2: never negative
         const uint32_t node = uint32_t(zc) * nxy + uint32_t(y) * uint32_t(nx) + uint32_t(x);
         const uint32_t elem = (uint32_t(zc) * uint32_t(ny) + uint32_t(y)) * qnx + uint32_t(x);
         const uint32_t vo = elem * EB;
         const bool ylo = y == 0, yhi = y == ny - 1;
         const bool zlo = zc == 0, zhi = zc == nz - 1;
-        if (valid) {
+        if constexpr (PL != 0) {
+            rprev = rcur;
+#pragma unroll
+            for (int i = 0; i < Q; ++i) fprev[i] = fcur[i];
+        }
+        if (valid && collides) {
             const float m[2] = {mval(rprev, 0), mval(rprev, 1)};
             const float rho[2] = {lds[sl(0)][0].at(pitch, ly + 1, lx + 1), lds[sl(0)][1].at(pitch, ly + 1, lx + 1)};
             float sig[2][3], u[2][3];
@@ -402,9 +419,9 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step_dev(StepAr
                 if (cx_of(i) != 0) {
                     xq[xslot_of(i)].at(pitch, ly, lx + 1) = w;
                     // periodic rows held whole: the wrap across the box's x faces
-                    if (!GHOST && span) {
-                        if (cx_of(i) > 0 && lx == tw - 1) xq[xslot_of(i)].at(pitch, ly, 0) = w;
-                        if (cx_of(i) < 0 && lx == 0) xq[xslot_of(i)].at(pitch, ly, tw + 1) = w;
+                    if (!GHOST) {
+                        if (cx_of(i) > 0 && wrap_hi) xq[xslot_of(i)].at(pitch, ly, 0) = w;
+                        if (cx_of(i) < 0 && wrap_lo) xq[xslot_of(i)].at(pitch, ly, tw + 1) = w;
                     }
                     return;
                 }
@@ -447,7 +464,7 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step_dev(StepAr
                                 (uint32_t(__builtin_bit_cast(unsigned short, __float2half_rn(rho[1]))) << 16);
             __builtin_amdgcn_raw_buffer_store_b32(rw, rf_out, 4u * node, 0, ST);
         }
-        if (GHOST && y < ny) {
+        if (GHOST && y < ny && z_ghosts) {
             // Populations streaming in from ghost nodes, which hold
             // g_eq(rho_b, A (x_g - x_c)) (values per weight: rho_b times the bracket).
             // The lane's coordinates pass through an empty asm first, so that what this
@@ -475,7 +492,7 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step_dev(StepAr
                 }
             }
         }
-        if (GHOST) {
+        if (GHOST && xy_ghosts) {
             // (a) Ghosts beside the tile's rows at x = -1 and x = nx: their five
             // populations with c_x pointing into the box stream into the face nodes of
             // the rows y + c_y, z + c_z, and enter the x exchange at the tile's edge
@@ -551,9 +568,11 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step_dev(StepAr
         // ---- 4. the c_x != 0 stores: lane x writes its own slot with the word pushed
         // from x - c_x (whole cache lines per wavefront); a tile that does not hold
         // whole rows also writes the one word that leaves it across each edge.
-        if (valid) {
+        // (PL: five directions per half)
+        if (valid && stores) {
 #pragma unroll
             for (int jx = 0; jx < NXD; ++jx) {
+                if (PL && jx / 5 != half) continue;
                 const int i = jx < 2 ? jx + 1 : jx + 5;
                 const int cx = cx_of(i), cy = cy_of(i), cz = cz_of(i);
                 int yd = y + cy, zd = zc + cz;

@@ -228,16 +228,15 @@ struct LdsPlane<T, 0, C, N> {
     __device__ __forceinline__ T &at(int pitch, int r, int c) { return v[r * pitch + c]; }
     __device__ __forceinline__ T *data() { return v; }
 };
-// Whether FIT_WAVES wavefronts can run tiles of w x h nodes: the node, ring (one node a thread) and ghost
+// Whether wx wavefronts can run tiles of w x h nodes: the node, ring (one node a thread) and ghost
 // counts the kernels assume.  The y-face tasks read window cells up to column 64 ceil(w / 64).
-__host__ __device__ constexpr bool fit_ok(int w, int h) {
-    return w >= 3 && h >= 1 && h <= FIT_ROWS && w <= FIT_WIDTH && w * h <= 64 * FIT_WAVES &&
-           2 * (w + 2) + 2 * h <= 64 * FIT_WAVES && 20 * h <= 64 * FIT_WAVES &&
-           h * (w + 2) + (w + 63) / 64 * 64 < window_cells(0, FIT_WAVES);
+__host__ __device__ constexpr bool fit_ok(int w, int h, int wx) {
+    return w >= 3 && h >= 1 && h <= FIT_ROWS && w <= FIT_WIDTH && w * h <= 64 * wx && 2 * (w + 2) + 2 * h <= 64 * wx &&
+           20 * h <= 64 * wx && h * (w + 2) + (w + 63) / 64 * 64 < window_cells(0, wx);
 }
 
-template <int P, int TY, int WX, bool GHOST, int WAVES, int ST>
-__global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a) {
+template <int P, int TY, int WX, bool GHOST, int WAVES, int ST, int PL = 0>
+__global__ __launch_bounds__(step_threads(TY, WX) * (PL ? PL : 1), WAVES) void k_step(StepArgs a) {
     using S = typename Prec<P>::S;
     using W = typename Prec<P>::W;
     using R = typename Prec<P>::R;
@@ -254,17 +253,25 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a
     // the next plane's populations (raw words, decoded when the plane is used, so
     // that nothing waits for them during the collision) are loaded while the
     // current one collides.  FP64 windows leave no registers for a third plane.
-    constexpr bool PREFETCH = sizeof(S) < 8;
+    constexpr bool PREFETCH = sizeof(S) < 8 && PL == 0;
     // the x-exchange values read from LDS together before their stores (FP32 storage)
-    constexpr bool BATCH = PREFETCH;
+    constexpr bool BATCH = sizeof(S) < 8;
     static_assert(!Prec<P>::DEV, "the 16-bit deviation formats run k_step_dev");
     // density window: the planes zc - 1, zc, zc + 1 of the collision and one more
-    constexpr int NSLOT = 4;
+    constexpr int NSLOT = PL ? PL : 4;
+    // PL planes at once: the threads of plane threadIdx.y load plane zs - 1 + threadIdx.y.  Then the inner
+    // planes' threads collide theirs, zc = zs + pair, and the outer ones', which have none, take that
+    // plane's ghosts; the c_x != 0 stores are shared between the threads that do not collide (PL = 3)
+    // or by the pair of planes (PL = 4).
+    static_assert(PL == 0 || (FIT && (PL == 3 || PL == 4)), "chunks of one or two planes, fitted tiles");
+    const int plane = PL ? int(threadIdx.y) : 0;
+    const int pair = PL == 4 ? plane >> 1 : 0;
     __shared__ LdsPlane<D, TY ? TY + 2 : 0, 64 * WX + 2, window_cells(TY, WX)> lds[NSLOT][2];
     // x exchange: post-collision values with c_x != 0, by component, slot, row and
     // column lx + 1; columns 0 and tw + 1 hold what streams in across the tile's
     // left and right edges (ghost populations, or the periodic wrap)
-    __shared__ LdsPlane<B, TY, 64 * WX + 2, exchange_cells(TY, WX)> xq[2][NXD];
+    __shared__ LdsPlane<B, TY, 64 * WX + 2, exchange_cells(TY, WX)> xqs[PL == 4 ? 2 : 1][2][NXD];
+    auto &xq = xqs[pair];
 
     const int tid = FIT ? int(threadIdx.x) : int(threadIdx.y) * TXW + int(threadIdx.x);
     const int ly = FIT ? tid / TXW : int(threadIdx.y), lx = FIT ? tid - ly * TXW : int(threadIdx.x);
@@ -299,11 +306,18 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a
     const int box = bz / a.nzc;
     const int zs = (bz % a.nzc) * a.zchunk;
     const int ze = min(zs + a.zchunk, a.nz);
+    const bool here = PL == 0 || zs + pair < ze;  // (the last chunk of an odd count of planes has one)
+    const bool collides = PL == 0 || (here && (plane == 1 || (PL == 4 && plane == 2)));
+    const bool xy_ghosts = PL == 0 || (here && (plane == 0 || (PL == 4 && plane == 3)));
+    const bool z_ghosts = PL == 0 || (here && (PL == 3 ? plane == 2 : (plane == 0 || plane == 3)));
+    const bool stores = PL == 0 || (here && !(PL == 3 && plane == 1));
+    const int half = PL == 3 ? plane >> 1 : plane & 1;  // which half of the stores
     const int x = x0 + lx, y = y0 + ly;
     const bool valid = (x < a.nx) && (y < a.ny) && (!FIT || ly < TYR);
     const int tw = min(TXW, a.nx - x0), th = min(TYR, a.ny - y0);  // valid tile extent
     const bool left_face = x0 == 0, right_face = x0 + tw == a.nx;
     const bool span = left_face && right_face;                     // the tile holds whole rows
+    const bool wrap_lo = span && lx == 0, wrap_hi = span && lx == tw - 1;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const uint32_t N = uint32_t(a.nnode);
     const uint32_t nxy = uint32_t(nx) * uint32_t(ny);
@@ -377,9 +391,9 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a
     if (PREFETCH) prefetch(zfirst);
 
     W fprev[2][Q], fcur[2][Q];
-    for (int k = 0; k < nplanes; ++k) {
-        const int z = zfirst + dir * k;
-        const int slot = k % NSLOT;
+    for (int k = PL ? 2 : 0; k < (PL ? 3 : nplanes); ++k) {
+        const int z = PL ? zs - 1 + plane : zfirst + dir * k;
+        const int slot = PL ? plane : k % NSLOT;
         // (fitted tiles: an empty asm keeps what is derived from the pitch in the march; hoisted
         // out of it, a row address per neighbour row, it spills)
         int pitch = LW;
@@ -466,14 +480,14 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a
         if (k >= 2) {
         // ---- 3. collide the previous plane of the march, zc = z - dir: c_x = 0
         // populations are pushed now, the others go through LDS ----
-        const int zc = z - dir;  // plane zc + d sits in LDS slot sl(d)
-        auto sl = [&](int d) { return (k - 1 + dir * d) % NSLOT; };  // k >= 2: never negative
+        const int zc = PL ? zs + pair : z - dir;  // plane zc + d sits in LDS slot sl(d)
+        auto sl = [&](int d) { return PL ? pair + 1 + d : (k - 1 + dir * d) % NSLOT; };  // k >= 2: never negative
         const uint32_t elem = (uint32_t(zc) * uint32_t(ny) + uint32_t(y)) * qnx + uint32_t(x);
         const uint32_t vo = elem * EB;
         const bool ylo = y == 0, yhi = y == ny - 1;
         const bool zlo = zc == 0, zhi = zc == nz - 1;
-        if (valid) {
-            const W (&f)[2][Q] = fprev;  // populations of plane zc, loaded one plane ago
+        if (valid && collides) {
+            const W (&f)[2][Q] = PL ? fcur : fprev;  // populations of plane zc, loaded one plane ago
             // moments, Eq. 6: density and momentum from pair sums and differences
             R rho[2], j[2][3];
 #pragma unroll
@@ -501,10 +515,14 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a
                     const D lo = lds[sl(-cz_of(i))][o].at(pitch, ly + 1 - cy_of(i), lx + 1 - cx_of(i));
                     e[p] = hi - lo;
                 }
+                // the multiply-adds written out: which of the two products a sum is fused with would
+                // else differ between the kernel's instances, and a state with the tile shape
+                static_assert(sizeof(D) == 8, "FP64 force stencil");
                 const D w1 = D(1) / D(18), w2 = D(1) / D(36);
-                sig[s][0] = w1 * e[1] + w2 * (e[4] + e[5] + e[6] + e[7]);
-                sig[s][1] = w1 * e[2] + w2 * (e[4] - e[5] + e[8] + e[9]);
-                sig[s][2] = w1 * e[3] + w2 * (e[6] - e[7] + e[8] - e[9]);
+                sig[s][0] = __builtin_fma(w1, e[1], w2 * (e[4] + e[5] + e[6] + e[7]));
+                sig[s][1] = __builtin_fma(w1, e[2], w2 * (e[4] - e[5] + e[8] + e[9]));
+                sig[s][2] = P == SCLBM_F64 ? __builtin_fma(w2, e[6] - e[7] + e[8] - e[9], w1 * e[3])
+                                           : __builtin_fma(w1, e[3], w2 * (e[6] - e[7] + e[8] - e[9]));
             }
             // common velocity u' and shifted velocity u' + tau_s F_s / rho_s = u' - G tau_s sig_s
             const R om0 = R(a.omega[0]), om1 = R(a.omega[1]);
@@ -548,9 +566,9 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a
                     if (cx_of(i) != 0) {
                         xq[s][xslot_of(i)].at(pitch, ly, lx + 1) = bits;
                         // periodic rows held whole: the wrap across the box's x faces
-                        if (!GHOST && span) {
-                            if (cx_of(i) > 0 && lx == tw - 1) xq[s][xslot_of(i)].at(pitch, ly, 0) = bits;
-                            if (cx_of(i) < 0 && lx == 0) xq[s][xslot_of(i)].at(pitch, ly, tw + 1) = bits;
+                        if (!GHOST) {
+                            if (cx_of(i) > 0 && wrap_hi) xq[s][xslot_of(i)].at(pitch, ly, 0) = bits;
+                            if (cx_of(i) < 0 && wrap_lo) xq[s][xslot_of(i)].at(pitch, ly, tw + 1) = bits;
                         }
                         return;
                     }
@@ -586,7 +604,7 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a
             const R usq = gx * gx + gy * gy + gz * gz;
             return R(1) + R(3) * cu + R(4.5) * cu * cu - R(1.5) * usq;
         };
-        if (GHOST && y < ny) {
+        if (GHOST && y < ny && z_ghosts) {
             // Populations streaming in from ghost nodes, which hold
             // g_eq(rho_b, A (x_g - x_c)).
             // (b) y and z faces: the directions whose source lies beyond y = 0, y = ny - 1,
@@ -606,7 +624,7 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a
                 }
             }
         }
-        if (GHOST) {
+        if (GHOST && xy_ghosts) {
             // (a) Ghosts beside the tile's rows at x = -1 and x = nx: their five
             // populations with c_x pointing into the box stream into the face nodes of
             // the rows y + c_y, z + c_z, and enter the x exchange at the tile's edge
@@ -676,7 +694,8 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a
         // pushed from x - c_x, so that every store of a wavefront covers 64 aligned
         // consecutive elements (whole cache lines).  A tile that does not hold whole
         // rows also writes the one value that leaves it across each edge.
-        if (valid && BATCH) {
+        // (PL: one component per half)
+        if (valid && BATCH && stores) {
             // FP32 storage: all ten values per component first, so that the LDS reads
             // overlap instead of each store waiting for its own read
             B wq[2][NXD];
@@ -684,7 +703,8 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a
             for (int jx = 0; jx < NXD; ++jx) {
                 const int cx = cx_of(jx < 2 ? jx + 1 : jx + 5);
 #pragma unroll
-                for (int s = 0; s < 2; ++s) wq[s][jx] = xq[s][jx].at(pitch, ly, lx + 1 - cx);
+                for (int s = 0; s < 2; ++s)
+                    if (!PL || s == half) wq[s][jx] = xq[s][jx].at(pitch, ly, lx + 1 - cx);
             }
             // destination row of direction i and whether it lies outside the box (ghost mode)
             auto dest_row = [&](int i, bool &out) -> uint32_t {
@@ -708,7 +728,8 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a
                 if (cx > 0 && lx == 0) ok = ok && (GHOST ? left_face : span);
                 if (cx < 0 && lx == tw - 1) ok = ok && (GHOST ? right_face : span);
 #pragma unroll
-                for (int s = 0; s < 2; ++s) Prec<P>::template bstore_bits<ST>(rd[s], ok ? (row + uint32_t(x)) * EB : kOOB, 0, wq[s][jx]);
+                for (int s = 0; s < 2; ++s)
+                    if (!PL || s == half) Prec<P>::template bstore_bits<ST>(rd[s], ok ? (row + uint32_t(x)) * EB : kOOB, 0, wq[s][jx]);
             }
             // a tile that does not hold whole rows also writes the value leaving it
             // across each edge, in a loop of its own so that no branch separates the
@@ -728,11 +749,12 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a
                     if (go) {
 #pragma unroll
                         for (int s = 0; s < 2; ++s)
-                            Prec<P>::template bstore_bits<ST>(rd[s], (row + uint32_t(xd)) * EB, 0, xq[s][jx].at(pitch, ly, lx + 1));
+                            if (!PL || s == half)
+                                Prec<P>::template bstore_bits<ST>(rd[s], (row + uint32_t(xd)) * EB, 0, xq[s][jx].at(pitch, ly, lx + 1));
                     }
                 }
             }
-        } else if (valid) {
+        } else if (valid && stores) {
             // FP64 storage (no registers left for the values): one read per store
 #pragma unroll
             for (int jx = 0; jx < NXD; ++jx) {
@@ -752,7 +774,8 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a
                 if (cx < 0 && lx == tw - 1) ok = ok && (GHOST ? right_face : span);
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
-                    Prec<P>::template bstore_bits<ST>(rd[s], ok ? (row + uint32_t(x)) * EB : kOOB, 0, xq[s][jx].at(pitch, ly, lx + 1 - cx));
+                    if (!PL || s == half)
+                        Prec<P>::template bstore_bits<ST>(rd[s], ok ? (row + uint32_t(x)) * EB : kOOB, 0, xq[s][jx].at(pitch, ly, lx + 1 - cx));
                 if (!span) {
                     const bool edge = cx > 0 ? lx == tw - 1 : lx == 0;
                     int xd = x + cx;
@@ -762,7 +785,8 @@ __global__ __launch_bounds__(step_threads(TY, WX), WAVES) void k_step(StepArgs a
                     if (go) {
 #pragma unroll
                         for (int s = 0; s < 2; ++s)
-                            Prec<P>::template bstore_bits<ST>(rd[s], (row + uint32_t(xd)) * EB, 0, xq[s][jx].at(pitch, ly, lx + 1));
+                            if (!PL || s == half)
+                                Prec<P>::template bstore_bits<ST>(rd[s], (row + uint32_t(xd)) * EB, 0, xq[s][jx].at(pitch, ly, lx + 1));
                     }
                 }
             }

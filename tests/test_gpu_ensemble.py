@@ -202,17 +202,8 @@ def test_moments_of_all_boxes_in_one_pass(sc):
         assert np.allclose(allm[b].cpu().numpy(), ref, rtol=1e-12, atol=1e-9)
 
 
-@pytest.mark.parametrize("bc", ["ghost", "periodic"])
-@pytest.mark.parametrize("prec", ["f64", "f32", "f16dev", "bf16dev"])
-@pytest.mark.parametrize("nxyz,nbox", [((21, 89, 20), 3), ((20, 130, 22), 4), ((150, 40, 30), 1), ((130, 61, 30), 1),
-                                       ((260, 31, 30), 1), ((97, 60, 33), 2), ((100, 120, 90), 1)])
-def test_fitted_tiles_equal_fixed_tiles(sc, nxyz, nbox, prec, bc):
-    """Boxes whose default launch takes tiles fitted to the row (whole rows of 20 to
-    100 nodes, the row count at its limit of 24, rows cut into two to four parts with a
-    narrower last one, a last tile of fewer rows) against 64 x 4 tiles in chunks
-    of three planes: the states of every box are the same bytes after seven steps, and the
-    cached stores that rows off the cache lines take write the same as the streaming
-    ones (100-node FP64 rows)."""
+def same_as_fixed_tiles(sc, nxyz, nbox, prec, bc):
+    """The default launch against 64 x 4 tiles in chunks of three planes, seven steps."""
     nx, ny, nz = nxyz
     lats = [sc.Lattice(nx, ny, nz, nbox=nbox, bc=bc, prec=prec, table_len=8, tau=(1.0, 1.2), g_ab=wl.G_AB,
                        rho_b=wl.ghost_densities(8.0)) for _ in range(2)]
@@ -233,3 +224,29 @@ def test_fitted_tiles_equal_fixed_tiles(sc, nxyz, nbox, prec, bc):
     assert np.array_equal(a, b)
     ra, rb = (t.cpu().numpy() for t in lats[0].fields(box=nbox - 1, velocity=False))
     assert np.isfinite(ra).all() and np.isfinite(rb).all()
+
+
+@pytest.mark.parametrize("bc", ["ghost", "periodic"])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16dev", "bf16dev"])
+@pytest.mark.parametrize("nxyz,nbox", [((21, 89, 20), 3), ((20, 130, 22), 4), ((150, 40, 30), 1), ((130, 61, 30), 1),
+                                       ((260, 31, 30), 1), ((97, 60, 33), 2), ((100, 120, 90), 1)])
+def test_fitted_tiles_equal_fixed_tiles(sc, nxyz, nbox, prec, bc):
+    """Boxes whose default launch takes tiles fitted to the row (whole rows of 20 to
+    100 nodes, the row count at its limit of 24, rows cut into two to four parts with a
+    narrower last one, a last tile of fewer rows) against 64 x 4 tiles in chunks
+    of three planes: the states of every box are the same bytes after seven steps, and the
+    cached stores that rows off the cache lines take write the same as the streaming
+    ones (100-node FP64 rows)."""
+    same_as_fixed_tiles(sc, nxyz, nbox, prec, bc)
+
+
+@pytest.mark.parametrize("bc", ["ghost", "periodic"])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f32d", "f16dev", "bf16dev"])
+@pytest.mark.parametrize("nxyz,nbox", [((3, 3, 3), 1), ((3, 50, 4), 1), ((32, 32, 32), 1), ((24, 21, 7), 3), ((45, 33, 29), 1),
+                                       ((40, 57, 33), 1), ((48, 48, 47), 1), ((128, 3, 5), 2), ((129, 5, 9), 1),
+                                       ((450, 3, 8), 1), ((21, 70, 9), 5)])
+def test_small_boxes_equal_fixed_tiles(sc, nxyz, nbox, prec, bc):
+    """Boxes that one workgroup per CU holds, with all planes of a chunk at once: chunks of
+    one and of two planes (odd counts: a last chunk of one), rows held whole and cut into up to four
+    parts with a narrower last one, tiles of one row and of all rows, several boxes."""
+    same_as_fixed_tiles(sc, nxyz, nbox, prec, bc)
