@@ -289,25 +289,36 @@ int one_round_zchunk(const sclbm_config &c, int ty, int wx) {
     return int((c.nz + nzc - 1) / nzc);
 }
 
+// Bytes of one population buffer, and whether both stay in the 256 MB memory-side cache from one step to the next.
+double state_bytes(const sclbm_config &c) { return double(c.nx) * c.ny * c.nz * c.nbox * 2 * Q * elem_bytes(c.prec); }
+bool side_cached(const sclbm_config &c) { return 2.0 * state_bytes(c) <= double(256 << 20); }
+// Bytes of a row's run of one direction.
+int row_bytes(const sclbm_config &c) { return c.nx * (is_dev(c.prec) ? 4 : int(elem_bytes(c.prec))); }
+
 // Fitted tiles for this configuration (w = 0: none): the row, or an equal part of it, wide, and as
 // many rows as FIT_WAVES wavefronts hold.  Chosen where the rounds model above puts them
-// at least 8 % ahead of the default tile, each further tile of a row counting 10 % (ring
+// at least 13 % ahead of the default tile, each further tile of a row counting 10 % (ring
 // columns that are one node wide, and stores that end inside a cache line).  Measured, us per
 // step, default tile -> fitted, both with the better store policy: FP32 130^3 248 -> 203 (44 x 11),
 // 150^3 370 -> 278 (75 x 6), 200^3 760 -> 587 (100 x 5); FP64 100 x 120 x 90 periodic 181 -> 172 (100 x 5);
-// BF16 150 x 93 x 67 51 -> 46 (50 x 10), 35 boxes of 21 x 89 x 20 147 -> 96 (21 x 24).  Without the
-// margin they lose where the row fills its tile (FP32 127-wide 79 -> 81, 57 x 48 x 196 40 -> 45:
-// the row pitch is not a constant any more), and without the 10 % where a row is cut into many
-// narrow tiles (FP64 223 x 111 x 52 in seven 209 -> 230).  FP64 arithmetic on FP32 storage spills with them.
+// BF16 150 x 93 x 67 51 -> 46 (50 x 10), 35 boxes of 21 x 89 x 20 147 -> 96 (21 x 24).  With a margin of 8 %
+// they lose as often as they win (FP16 134 x 33 x 68 24.7 -> 28.5, BF16 101 x 161 x 131 x 2 204 -> 214; FP32 183 x 96 x 39 x 2
+// 124 -> 121), and without the 10 % where a row is cut into many narrow tiles (FP64 223 x 111 x 52 in seven 209 -> 230).
+// Not fitted: rows that the tile would cut although they start on cache lines or halves of them (FP64 176 x 43 x 40 x 4
+// 207 -> 238, 232 x 102 x 74 260 -> 308), or although one tile holds them (FP16 43 x 182 x 196 x 4 306 -> 360 in two);
+// narrow FP32 rows and 256-wide 16-bit tiles whose state streams from memory (FP32 43 x 174 x 48 x 16
+// 544 -> 580, periodic 31 x 87 x 27 x 16 114 -> 132, FP16 191 x 113 x 131 x 3 410 -> 444, where the fixed ones' wavefronts load whole lines);
+// FP64 arithmetic on FP32 storage, which spills with them.
 void default_fit(const sclbm_config &c, int &w, int &h, int &zc) {
     w = h = zc = 0;
-    if (c.prec == SCLBM_F32D) return;
     int ty, wx;
     default_tile(c, ty, wx);
+    if (c.prec == SCLBM_F32D || (wx == 4 && !side_cached(c))) return;
+    if (c.prec == SCLBM_F32 && c.nx <= 64 && (c.bc == SCLBM_BC_GHOST ? state_bytes(c) > double(256 << 20) : !side_cached(c))) return;
     long cost;
     default_zchunk(c, ty, wx, &cost);
-    double best = 0.92 * double(cost) * (1.0 + 0.1 * ((c.nx - 1) / (64 * wx)));
-    for (int ntx = 1; ntx <= 8; ++ntx) {
+    double best = 0.87 * double(cost) * (1.0 + 0.1 * ((c.nx - 1) / (64 * wx)));
+    for (int ntx = 1; ntx <= (c.nx <= FIT_WIDTH || row_bytes(c) % 64 == 0 ? 1 : 8); ++ntx) {
         const int fw = (c.nx + ntx - 1) / ntx;
         int fh = std::min(64 * FIT_WAVES / fw, FIT_ROWS);
         while (fh > 0 && !fit_ok(fw, fh, FIT_WAVES)) --fh;
@@ -354,21 +365,27 @@ SmallShape small_tiles(const sclbm_config &c, int &w, int &h) {
     return SmallShape{};
 }
 
-// Store policy of a launch with tiles w nodes wide: cached where the rows' runs of one direction
-// do not start on cache lines.  Then a line's two parts are written some time apart, and streaming
-// stores send each to memory by itself.  Measured, us per step, streaming -> cached: FP32 97 x 124 x 90
-// 93 -> 88, 190^3 783 -> 623; BF16 150 x 93 x 67 59 -> 49; 144 x 69 x 145 79 -> 66.  On whole lines the cached
-// ones cost L2 the rows that are read again: FP32 128^3 126 -> 134, FP64 96 x 125 x 90 153 -> 165.  Two cases
-// between: FP64 rows of even length (FP64 90^3 125 -> 130, 72^3 71 -> 61) and the 256-wide tile of the 16-bit
-// formats (200^3 330 -> 341, 222 x 49 x 64 38 -> 35) gain only while both population buffers fit
-// the 256 MB memory-side cache, or, FP64, where tiles cut the rows (150^3 658 -> 615).
-bool cached_stores(const sclbm_config &c, int w) {
-    const bool dev = is_dev(c.prec);
-    if (c.nx * (dev ? 4 : int(elem_bytes(c.prec))) % 128 == 0) return false;
-    const double state = double(c.nx) * c.ny * c.nz * c.nbox * 2 * Q * elem_bytes(c.prec);
-    if (2.0 * state <= double(256 << 20)) return true;
-    if (c.prec == SCLBM_F64) return c.nx % 2 != 0 || w < c.nx;
-    return !(dev && w >= 256);
+// Store policy of a launch with tiles w nodes wide.  Where the rows' runs of one direction do not start
+// on cache lines, a line's two parts are written some time apart, and streaming stores send each to memory by
+// itself; cached ones join them in the L2, at the price of rows that are read again.  Measured, us per step, streaming -> cached:
+// - Up to 22 MB of one buffer (the L2 caches hold 32 MB) nothing is gained and the writes wait for the end of
+//   the kernel: FP16 41 x 26 x 128 16.5 -> 17.5, BF16 143 x 26 x 36 periodic 14.5 -> 16.0; at 23 - 26 MB FP16 33 x 72 x 128
+//   26.7 -> 23.7, FP32 23 x 165 x 22 x 2 26.1 -> 21.5.  FP64 arithmetic on FP32 storage up to 32 MB, rows held whole (72 x 92 x 31
+//   25.2 -> 26.5; 179 x 35 x 31 32.7 -> 30.1).
+// - Both buffers in the memory-side cache: cached, rows on whole lines too (FP32 64 x 84 x 34 x 3 41.6 -> 36.2, 97 x 124 x 90
+//   93 -> 88; FP64 72^3 71 -> 61; BF16 150 x 93 x 67 59 -> 49).
+// - Beyond it, rows of whole lines or halves of them stream (FP32 128^3 126, cached 134; 112 x 25 x 56 x 16 186, 197; FP64 96 x 125 x 90
+//   153, 165), and 256-wide 16-bit tiles (200^3 330, 341); other rows are cached (FP32 190^3 783 -> 623, 37 x 169 x 153 x 4
+//   462 -> 390).  In FP64: rows that tiles cut (150^3 658 -> 615); fitted tiles unless rows are whole 32-byte sectors
+//   (34 x 95 x 125 x 4 320 -> 272, 30 x 139 x 181 x 2 313 -> 259; 92 x 105 x 94 3 % slower); fixed ones for odd rows above 320 MB
+//   (57 x 146 x 198 x 2 537 -> 494; 111 x 41 x 163 124 -> 133).
+bool cached_stores(const sclbm_config &c, int w, bool fitted) {
+    const bool cut = w < c.nx;
+    if (state_bytes(c) <= double((c.prec == SCLBM_F32D && !cut ? 32 : 22) << 20)) return false;
+    if (side_cached(c)) return true;
+    if (row_bytes(c) % 64 == 0) return false;
+    if (c.prec == SCLBM_F64) return cut || (fitted ? row_bytes(c) % 32 != 0 : c.nx % 2 != 0 && state_bytes(c) > double(320 << 20));
+    return !(is_dev(c.prec) && w >= 256);
 }
 
 // Launch of the step kernel for precision P, a tile of TY rows of WX wavefronts (TY = 0: fitted tiles of
@@ -439,7 +456,7 @@ template <int P>
 hipError_t launch_step(sclbm_ctx *c, const StepArgs &a) {
     if (a.tile_w && c->small.planes) return launch_step_small<P>(c, a);
     const int w = a.tile_w ? a.tile_w : 64 * c->tile_waves;
-    return cached_stores(c->cfg, w) ? launch_step_st<P, kStoreCached>(c, a) : launch_step_st<P, kStoreNT>(c, a);
+    return cached_stores(c->cfg, w, a.tile_w != 0) ? launch_step_st<P, kStoreCached>(c, a) : launch_step_st<P, kStoreNT>(c, a);
 }
 
 hipError_t launch_step_prec(sclbm_ctx *c, const StepArgs &a) {

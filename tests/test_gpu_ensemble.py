@@ -229,14 +229,13 @@ def same_as_fixed_tiles(sc, nxyz, nbox, prec, bc):
 @pytest.mark.parametrize("bc", ["ghost", "periodic"])
 @pytest.mark.parametrize("prec", ["f64", "f32", "f16dev", "bf16dev"])
 @pytest.mark.parametrize("nxyz,nbox", [((21, 89, 20), 3), ((20, 130, 22), 4), ((150, 40, 30), 1), ((130, 61, 30), 1),
-                                       ((260, 31, 30), 1), ((97, 60, 33), 2), ((100, 120, 90), 1)])
+                                       ((260, 31, 30), 1), ((97, 60, 33), 2), ((100, 120, 90), 1),
+                                       ((150, 93, 67), 1), ((130, 90, 90), 1)])
 def test_fitted_tiles_equal_fixed_tiles(sc, nxyz, nbox, prec, bc):
     """Boxes whose default launch takes tiles fitted to the row (whole rows of 20 to
     100 nodes, the row count at its limit of 24, rows cut into two to four parts with a
     narrower last one, a last tile of fewer rows) against 64 x 4 tiles in chunks
-    of three planes: the states of every box are the same bytes after seven steps, and the
-    cached stores that rows off the cache lines take write the same as the streaming
-    ones (100-node FP64 rows)."""
+    of three planes: the states of every box are the same bytes after seven steps."""
     same_as_fixed_tiles(sc, nxyz, nbox, prec, bc)
 
 
