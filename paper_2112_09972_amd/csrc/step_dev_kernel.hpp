@@ -235,7 +235,9 @@ __global__ __launch_bounds__(step_threads(TY, WX) * (PL ? PL : 1), WAVES) void k
     const int tw = min(TXW, a.nx - x0), th = min(TYR, a.ny - y0);
     const bool left_face = x0 == 0, right_face = x0 + tw == a.nx;
     const bool span = left_face && right_face;
-    const bool wrap_lo = span && lx == 0, wrap_hi = span && lx == tw - 1;
+    // rows held whole, periodic: which lanes also push across the box's x faces (one condition each: as two,
+    // the compiler may split the pushes' blocks, and with them contract the arithmetic otherwise)
+    const bool wrap_lo = !GHOST && span && lx == 0, wrap_hi = !GHOST && span && lx == tw - 1;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const uint32_t N = uint32_t(a.nnode);
     const uint32_t nxy = uint32_t(nx) * uint32_t(ny);
