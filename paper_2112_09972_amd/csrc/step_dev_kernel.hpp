@@ -20,8 +20,8 @@
 // 72 w_i, so their FP32 rounding biases neither mass nor momentum.  The
 // functions run with contraction off, so that every tile shape rounds alike.
 //
-// Tiling, march along z, density ring, x exchange through LDS, tile order and
-// stores are those of k_step, with a 3-slot density window (planes zc - 1, zc,
+// Tiling (fixed, fitted, several planes at once), march along z, density ring, x exchange through LDS, tile
+// order and stores are those of k_step, with a 3-slot density window (planes zc - 1, zc,
 // zc + 1) and, beside every density, the node's (m, 1 / m) per component that a
 // value pushed into the node is encoded against.
 #pragma once

@@ -34,8 +34,17 @@
 // wavefront covers 64 aligned consecutive elements, i.e. whole cache lines.
 // (Shifted stores leave partial lines that another wavefront completes later;
 // the same access pattern without arithmetic runs at 3.7 TB/s with shifted
-// stores and 5.1 TB/s with whole-line ones.)  Stores are non-temporal where rows start on
-// cache lines, else cached (ST; kStoreNT).
+// stores and 5.1 TB/s with whole-line ones.)  Stores are non-temporal or cached (ST, kStoreNT), by the rows'
+// alignment and the size of the state.
+//
+// Shapes of a workgroup.  Three, all with the same arithmetic (a state does not depend on them):
+// - fixed tiles (TY, WX): where rows fill them.  HBM-bound: 126 us per launch of the FP32 128^3 box, 5.0 TB/s in
+//   algorithmic bytes.
+// - fitted tiles (TY = 0): the row, or an equal part of it, wide and as many rows as the threads hold, where a fixed
+//   tile leaves many lanes idle (FP32 150^3 370 -> 278 us).
+// - PL planes at once (TY = 0, PL = 3 or 4): no march, every plane of a chunk of one or two on wavefronts of its own, for
+//   boxes that one workgroup per CU holds.  Those are bound by latency: a march costs two loads, two barriers and
+//   a collision per plane in turn, this one load, two barriers and a collision in all (FP64 32^3 22.2 -> 8.9 us).
 //
 // Precision.  FP64 storage computes in FP64.  FP32 storage computes the
 // collision in FP32 (or FP64: SCLBM_F32D); the densities of the force
