@@ -16,7 +16,7 @@
 // 8-byte stores from registers, and the copy whose contraction runs over the columns (the
 // next layer's input) passes through a wavefront's own 2.5 KB of LDS.
 //
-// One training step of up to 1024 rows is eight launches: input, three layers, output layer with
+// One training step of up to 2048 rows is eight launches: input, three layers, output layer with
 // its loss and input gradient, two hidden input gradients, and all parameter gradients with
 // Adam.  At 256 rows each lasts as long as its chain of memory latencies (launch, arguments,
 // operands from the other XCDs' side of the cache, stores), 3.5 to 7 us, 11 us the last, which
