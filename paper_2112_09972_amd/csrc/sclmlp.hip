@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -117,6 +118,7 @@ struct sclmlp_ctx {
     int device = 0;
     int64_t step = 0;
     hipEvent_t inputs = nullptr, results = nullptr;  // order against another stream (no timing)
+    std::mutex ordering;  // held from an event's record to its wait: threads may share a context
 
     template <class T>
     T *at(size_t off) const { return reinterpret_cast<T *>(ws + off); }
@@ -239,6 +241,7 @@ sclbm_status sclmlp_after_stream(sclmlp_ctx *c, void *hip_stream) {
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (s == c->stream) return SCLBM_OK;
     TRY(use_device(c));
+    std::lock_guard<std::mutex> lock(c->ordering);
     HIP_TRY(hipEventRecord(c->inputs, s));
     HIP_TRY(hipStreamWaitEvent(c->stream, c->inputs, 0));
     return SCLBM_OK;
@@ -249,6 +252,7 @@ sclbm_status sclmlp_before_stream(sclmlp_ctx *c, void *hip_stream) {
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (s == c->stream) return SCLBM_OK;
     TRY(use_device(c));
+    std::lock_guard<std::mutex> lock(c->ordering);
     HIP_TRY(hipEventRecord(c->results, c->stream));
     HIP_TRY(hipStreamWaitEvent(s, c->results, 0));
     return SCLBM_OK;

@@ -299,3 +299,39 @@ def test_gradients_and_fused_step_over_batch_sizes(env, n):
     # the BF16 copies of both orders follow: the next forward and backward agree too
     assert net.gradients(*dev).item() == other.gradients(*dev).item()
     assert np.array_equal(net.grads(), other.grads())
+
+
+def test_threads_share_a_network_from_their_own_streams(env):
+    """Four threads predict on one context, each from its own stream whose input is
+    still being written when the call is made: every result equals the one-thread
+    result on the same windows (same kernel, same bits)."""
+    import threading
+    torch, mlp = env
+    net = mlp.Network(max_batch=512)
+    net.set_params(mlp.init_params(3))
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    base = [torch.randn((300, 576), generator=gen, device="cuda:0") for _ in range(4)]
+    want = [[net.predict(b * (k + 1.0)).clone() for k in range(25)] for b in base]
+    torch.cuda.synchronize()
+    got = [[] for _ in base]
+
+    def work(i):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            for k in range(25):
+                slow = torch.ones((512, 512), device="cuda:0")
+                for _ in range(8):
+                    slow = (slow @ slow) * (1.0 / 512.0)      # the input follows these on the stream
+                got[i].append(net.predict(base[i] * (k + slow[0, 0])))
+        stream.synchronize()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for i in range(4):
+        assert len(got[i]) == 25
+        for k in range(25):
+            assert torch.equal(got[i][k], want[i][k]), (i, k)
