@@ -95,17 +95,19 @@ __global__ __launch_bounds__(MM_THREADS) void k_mm_quad(MmArgs a) {
         for (int e = first; e < NS * MM_QUAD_TRAJ; e += step) {
             const int tr = e / NS, m = e % NS;
             const int64_t t = min(t0 + tr, a.ntraj - 1);
-            // row and fraction of the m-th half substep; a time beyond the table is taken at its end
-            const uint32_t hs = 2u * uint32_t(s0) + uint32_t(m), per = 2u * uint32_t(a.substeps);
-            int64_t n = n0 + hs / per;
-            uint32_t f = hs % per;
+            // row n and fraction f / (2 substeps) of the m-th half substep (past the table: its end).  At
+            // f = 0 the matrix is row n's alone: a record depends on no row after its own, which may
+            // hold anything (tables of several lengths are padded, with NaN for one)
+            const uint32_t sub = uint32_t(s0) + uint32_t(m >> 1);
+            int64_t n = n0 + sub / uint32_t(a.substeps);
+            uint32_t f = 2u * (sub % uint32_t(a.substeps)) + uint32_t(m & 1);
             if (n >= a.nrows - 1) {
-                n = a.nrows - 2;
-                f = per;
+                n = a.nrows - 1;
+                f = 0;
             }
             const double *p = a.A + (t * a.nrows + n) * 9;
             double L[9];
-            mm_matrix(a, p, p + 9, double(f) * (0.5 / double(a.substeps)), L);
+            mm_matrix(a, p, f ? p + 9 : p, double(f) * (0.5 / double(a.substeps)), L);
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
                 const int j1 = (j + 1) % 3, j2 = (j + 2) % 3;

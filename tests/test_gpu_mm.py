@@ -49,3 +49,26 @@ def test_mm_chunks_and_starts(ntraj, nrows, substeps, every, start):
         ref = mm.integrate(A[t].reshape(nrows, 3, 3), 19.0, 1.3, substeps=substeps, record_every=every,
                            M0=None if M0 is None else M0[t].reshape(3, 3))
         assert np.abs(got[t] - ref).max() <= 3e-13, (t, np.abs(got[t] - ref).max())
+
+
+@pytest.mark.parametrize("fill", [np.nan, np.inf])
+@pytest.mark.parametrize("ntraj,nrows,valid,substeps,start", [
+    (3, 12, 2, 1, "I"), (17, 40, 9, 1, "I"), (17, 40, 8, 2, "I"), (5, 30, 23, 3, "I"), (4, 12, 1, 1, "I"),
+    (8193, 7, 4, 1, "I"), (70, 12, 5, 2, "M0")])
+def test_mm_records_do_not_depend_on_later_rows(ntraj, nrows, valid, substeps, start, fill):
+    """Tables padded past their `valid` rows (with NaN or infinity): every record up
+    to row valid - 1 holds the same bytes as with a table of `valid` rows, at and
+    off the edges of the eight-substep chunks; the records after it are not finite."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2112_09972_amd as sc
+    rng = np.random.default_rng(ntraj + valid)
+    A = 0.02 * rng.standard_normal((ntraj, nrows, 9))
+    A[:, valid:] = fill
+    M0 = None if start == "I" else np.eye(3).reshape(9) + 0.1 * rng.standard_normal((ntraj, 9))
+    got = sc.mm_integrate(A, 19.0, 1.3, substeps=substeps, M0=M0).cpu().numpy()
+    want = sc.mm_integrate(A[:, :valid], 19.0, 1.3, substeps=substeps, M0=M0).cpu().numpy()
+    assert np.isfinite(want).all()
+    assert np.array_equal(got[:, :valid], want)
+    assert not np.isfinite(got[:, valid:]).any()
