@@ -4,6 +4,7 @@
 #pragma once
 
 #include "aux_kernels.hpp"
+#include "wave.hpp"
 
 namespace sclbm {
 
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(NRED_THREADS) void k_surface(const double *phi, Box
     double v[2] = {0.0, 0.0};
     int count = 0;  // noted cells, the same in every lane
     auto cut = [&]() {
-        __builtin_amdgcn_wave_barrier();  // the list's writes stand before its reads (one wavefront, in order)
+        wave_lds_sync();  // the list's writes stand before its reads
         for (int e = lane; e < 6 * count; e += 64) {
             const uint32_t c = mine[e / 6];
             const int t = e % 6;
@@ -133,6 +134,7 @@ __global__ __launch_bounds__(NRED_THREADS) void k_surface(const double *phi, Box
             ss[3] = phi[c + 1u + nx + nxy];
             tet_cut(pp, ss, v[0], v[1]);
         }
+        wave_lds_sync();  // and those before the next writes
         count = 0;
     };
     // every lane of a wavefront stays in the loop until its last one is done

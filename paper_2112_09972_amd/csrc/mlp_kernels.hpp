@@ -29,6 +29,8 @@
 
 #include <type_traits>
 
+#include "wave.hpp"
+
 namespace sclmlp {
 
 typedef __bf16 bf16;
@@ -61,7 +63,8 @@ __host__ __device__ __forceinline__ size_t frag_index(size_t n, size_t k, size_t
 }
 constexpr size_t FRAG = 512;  // elements of a fragment
 
-__device__ __forceinline__ uint4 ld16(const bf16 *p) { return *reinterpret_cast<const uint4 *>(p); }
+// 16 bytes of bf16 (loaded as a vector of them: as the elements were stored)
+__device__ __forceinline__ uint4 ld16(const bf16 *p) { return __builtin_bit_cast(uint4, *reinterpret_cast<const bf16x8 *>(p)); }
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -265,12 +268,12 @@ __global__ __launch_bounds__(64 * W * W) void k_layer(LayerArgs g) {
                 *reinterpret_cast<bf16x4 *>(g.CT + at(i, j, q)) = h;
             }
             if (g.C) {
-                __builtin_amdgcn_wave_barrier();  // the wavefront's own tile: its LDS accesses keep their order
+                sclbm::wave_lds_sync();  // the wavefront's own tile
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
                     *reinterpret_cast<uint4 *>(g.C + ((size_t)(rt + i) * (NHID / 16) + (ct + j) * 2 + t) * FRAG + lane * 8) =
                         ld16(Cs + c31 * LDC + t * 16 + hi * 8);
-                __builtin_amdgcn_wave_barrier();
+                sclbm::wave_lds_sync();
             }
         }
 }
@@ -710,7 +713,7 @@ __global__ __launch_bounds__(256) void k_grad(GradArgs g) {
                     *reinterpret_cast<bf16x4 *>(wt + ((size_t)(ct * (NHID / 16) + rt * 2 + (q >> 1)) * 64 + c31 + 32 * (q & 1)) * 8 +
                                                 4 * hi) = h;
             }
-            __builtin_amdgcn_wave_barrier();
+            sclbm::wave_lds_sync();
 #pragma unroll
             for (int t = 0; t < 2; ++t)
                 *reinterpret_cast<uint4 *>(w + ((size_t)rt * (K / 16) + ct * 2 + t) * FRAG + lane * 8) =
@@ -813,7 +816,7 @@ __global__ __launch_bounds__(256) void k_adam(AdamArgs a) {
             // lane l: the 8 rows of column l
             bf16(*const T)[72] = tile[threadIdx.x >> 6];
             *reinterpret_cast<bf16x8 *>(&T[lane >> 3][(lane & 7) * 8]) = h;
-            __builtin_amdgcn_wave_barrier();
+            sclbm::wave_lds_sync();
 #pragma unroll
             for (int e = 0; e < 8; ++e) h[e] = T[e][lane];
             *reinterpret_cast<bf16x8 *>(wt + frag_index(k - (lane & 7) * 8 + lane, n - (lane >> 3), NHID)) = h;

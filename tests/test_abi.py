@@ -166,3 +166,17 @@ def test_mm_semi_axes_host_call():
     ref = np.sqrt(np.linalg.eigvalsh(0.5 * (Ms + Ms.transpose(0, 2, 1)))[:, ::-1])
     assert np.allclose(got, ref, rtol=1e-10, atol=1e-12)
     assert np.all(np.diff(got, axis=1) <= 0)
+
+
+def test_lane_exchanges_through_lds_are_fenced():
+    """The wavefront barrier builtin orders execution, not memory: kernels order the LDS
+    writes and reads of a wavefront's lanes with wave_lds_sync(), which has the fences,
+    and use the bare builtin nowhere."""
+    csrc = os.path.join(ROOT, "paper_2112_09972_amd", "csrc")
+    users = {}
+    for name in sorted(os.listdir(csrc)):
+        with open(os.path.join(csrc, name)) as fh:
+            text = re.sub(r"//[^\n]*", "", fh.read())
+        users[name] = (text.count("__builtin_amdgcn_wave_barrier"), text.count("__builtin_amdgcn_fence"))
+    assert users.pop("wave.hpp") == (1, 2)
+    assert all(n == (0, 0) for n in users.values()), users
