@@ -467,10 +467,14 @@ class Lattice:
     def autotune(self, trial_steps=20, cache=True):
         """Pick the fastest launch shape (clobbers the populations: call before
         an init).  Results are cached in $XDG_CACHE_HOME/sclbm/tuning.json keyed
-        by device, box shape, boxes, precision and boundary mode."""
+        by device, box shape, boxes, precision, boundary mode and the library's
+        contents: what a shape runs, and how fast, is a matter of the build."""
+        import hashlib
         import json
-        key = "%s|%dx%dx%d|%d|%d|%d|rowtiles5" % (self.torch.cuda.get_device_properties(self.device).name, self.nx,
-                                                 self.ny, self.nz, self.nbox, self.cfg.prec, self.cfg.bc)
+        with open(LIB_PATH, "rb") as fh:
+            build = hashlib.sha256(fh.read()).hexdigest()[:16]
+        key = "%s|%dx%dx%d|%d|%d|%d|%s" % (self.torch.cuda.get_device_properties(self.device).name, self.nx,
+                                           self.ny, self.nz, self.nbox, self.cfg.prec, self.cfg.bc, build)
         path = os.path.join(os.environ.get("XDG_CACHE_HOME", os.path.expanduser("~/.cache")), "sclbm", "tuning.json")
         table = {}
         if cache and os.path.exists(path):
