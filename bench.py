@@ -178,7 +178,7 @@ def precision_study(sc, nsteps: int):
         series[prec] = (np.array([x["semi_axes"] for x in st]), np.array([x["deformation"] for x in st]))
         ty, zc, wx = lat.get_launch()
         r = {"mlups": round(nodes * STRIDE * ns / el / 1e6, 1), "bytes_per_update": bpl[prec],
-             "launch": {"tile_rows": ty, "zchunk": zc, "tile_waves": wx},
+             "launch": {"tile_rows": ty, "zchunk": zc, "tile_waves": wx}, "tiles": lat.get_tiles(),
              "mass_drift_rel": [float(v) for v in (m1 - m0) / m0]}
         if prec != "f64":
             a64, d64 = series["f64"]
@@ -363,7 +363,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": case.name, "box": case.n, "radius": case.radius, "lattice_steps_per_step": STRIDE,
                    "lattice_steps_timed": STRIDE * K, "tau": case.tau, "g_ab": wl.G_AB,
-                   "storage": "fp32 row-blocked SoA, 2x19 populations", "arithmetic": "fp32 (fp64 totals and moments)", "launch": {"tile_rows": ty, "zchunk": zc, "tile_waves": wx},
+                   "storage": "fp32 row-blocked SoA, 2x19 populations", "arithmetic": "fp32 (fp64 totals and moments)", "launch": {"tile_rows": ty, "zchunk": zc, "tile_waves": wx}, "tiles": lat.get_tiles(),
                    "ca_max": round(float(ca.max()), 4), "ca_mean": round(float(ca.mean()), 4),
                    "mass_drift_rel": [float(v) for v in ((m1 - m0) / m0)],
                    "semi_axes_last": [round(float(v), 4) for v in axes[-1]]},

@@ -287,10 +287,16 @@ sclbm_status sclbm_load(sclbm_ctx *ctx, const void *host_buf, size_t bytes);
  * 1..64); the 16-bit formats take (4, 4) where the row's last 256-wide tile is
  * full or holds more than 160 nodes.  The default z-chunk minimises (rounds of
  * resident workgroups) x (planes per chunk + 2), at most 64 planes for the
- * 16-bit formats.  Where the default shape would leave many lanes beyond the row's end, tiles
- * fitted to the row run in its place (an autotuner candidate like any other, reported as
- * the default shape); every other shape runs as given.  The shape only changes speed, never results.  Pointers of get_launch may be NULL. */
+ * 16-bit formats.  The shape only changes speed, never results.
+ *
+ * A context starts at the default shape, of which the step makes what suits the box
+ * best (sclbm_default_tiles): that shape, or in its place tiles fitted to the row or all
+ * planes of a chunk at once, with streaming or cached stores.  A shape set with
+ * sclbm_set_launch, the default one included, runs as it is named, with streaming
+ * stores, until sclbm_reset_launch returns to the start.  get_launch reports the
+ * shape (the default one at the start; pointers may be NULL). */
 sclbm_status sclbm_set_launch(sclbm_ctx *ctx, int32_t tile_rows, int32_t zchunk, int32_t tile_waves);
+sclbm_status sclbm_reset_launch(sclbm_ctx *ctx);
 sclbm_status sclbm_get_launch(const sclbm_ctx *ctx, int32_t *tile_rows, int32_t *zchunk, int32_t *tile_waves);
 
 /* The launch shape a context with this configuration starts with (the
@@ -298,13 +304,29 @@ sclbm_status sclbm_get_launch(const sclbm_ctx *ctx, int32_t *tile_rows, int32_t 
  * NULL.  Errors: EINVAL for an invalid configuration. */
 sclbm_status sclbm_default_launch(const sclbm_config *cfg, int32_t *tile_rows, int32_t *zchunk, int32_t *tile_waves);
 
+/* What the step kernel runs: the kind of tiles (sclbm_tiles), a tile's nodes in a row and
+ * rows, planes per chunk, and whether its stores are cached (1) or streaming (0).
+ * get_tiles: of a context now; default_tiles: of a context with this configuration
+ * at its start, on the host without a device.  Pointers may be NULL.  Errors: EINVAL
+ * for an invalid configuration. */
+typedef enum {
+    SCLBM_TILES_FIXED = 0,  /* 64 tile_waves x tile_rows nodes, marching through a chunk of planes */
+    SCLBM_TILES_FITTED = 1, /* the row, or an equal part of it, wide; marching */
+    SCLBM_TILES_PLANES = 2  /* all planes of a chunk of one or two at once (small boxes) */
+} sclbm_tiles;
+sclbm_status sclbm_get_tiles(const sclbm_ctx *ctx, int32_t *kind, int32_t *width, int32_t *rows, int32_t *zchunk,
+                             int32_t *cached);
+sclbm_status sclbm_default_tiles(const sclbm_config *cfg, int32_t *kind, int32_t *width, int32_t *rows, int32_t *zchunk,
+                                 int32_t *cached);
+
 /* Library infrastructure, autotuner: time trial_steps steps (after one warm-up
- * step) for every tile shape ((4, 1), (8, 1), (4, 2) when nx > 64, (4, 4) for
- * the 16-bit formats when nx > 128) and z-chunk (2, 4, 8, 16, 32, 64, capped at nz, the
- * tile's default z-chunk, so the default launch is one of the candidates, and
- * the chunk that puts all workgroups in one round of resident ones, if any),
- * keep the fastest and set it.  The output pointers
- * (may be NULL) receive its shape and the best average step time in ms.
+ * step) for the launch a context starts with and for every tile shape ((4, 1), (8, 1),
+ * (4, 2) when nx > 64, (4, 4) for the 16-bit formats when nx > 128) and z-chunk (2, 4,
+ * 8, 16, 32, 64, capped at nz, the tile's default z-chunk, and the chunk that puts
+ * all workgroups in one round of resident ones, if any) as named shapes, keep the
+ * fastest and set it.  The output pointers (may be NULL) receive its shape (the
+ * default one where the start won; sclbm_get_tiles tells what runs) and the best
+ * average step time in ms.
  * The trials overwrite the populations (call it before an init call, or
  * re-initialise after) but restore the time.  In ghost mode every box's table
  * must cover steps n .. n + trial_steps.  Synchronises. */

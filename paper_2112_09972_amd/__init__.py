@@ -53,7 +53,8 @@ EXPORTS = [
     "sclbm_workspace_bytes", "sclbm_create", "sclbm_destroy", "sclbm_init_droplet", "sclbm_init_fields",
     "sclbm_set_gradient_table", "sclbm_step", "sclbm_get_step", "sclbm_fields", "sclbm_totals",
     "sclbm_droplet_moments", "sclbm_droplet_from_moments", "sclbm_droplet", "sclbm_velocity_error",
-    "sclbm_state_bytes", "sclbm_save", "sclbm_load", "sclbm_set_launch", "sclbm_get_launch", "sclbm_default_launch",
+    "sclbm_state_bytes", "sclbm_save", "sclbm_load", "sclbm_set_launch", "sclbm_reset_launch", "sclbm_get_launch",
+    "sclbm_default_launch", "sclbm_get_tiles", "sclbm_default_tiles",
     "sclbm_last_error", "sclbm_step_graph", "sclbm_autotune", "sclbm_droplet_moments_all", "sclbm_mm_integrate",
     "sclbm_droplet_surface_all", "sclbm_deformation_lbm", "sclbm_droplet_mass_all", "sclbm_reinject",
     "sclbm_droplet_moments_all_static", "sclbm_set_gradient", "sclbm_init_uniform", "sclbm_set_health_check",
@@ -112,8 +113,11 @@ def _load_library():
         "sclbm_save": [P, P, ctypes.c_size_t],
         "sclbm_load": [P, P, ctypes.c_size_t],
         "sclbm_set_launch": [P, I32, I32, I32],
+        "sclbm_reset_launch": [P],
         "sclbm_get_launch": [P, ctypes.POINTER(I32), ctypes.POINTER(I32), ctypes.POINTER(I32)],
         "sclbm_default_launch": [cfgp, ctypes.POINTER(I32), ctypes.POINTER(I32), ctypes.POINTER(I32)],
+        "sclbm_get_tiles": [P] + [ctypes.POINTER(I32)] * 5,
+        "sclbm_default_tiles": [cfgp] + [ctypes.POINTER(I32)] * 5,
         "sclmlp_workspace_bytes": [I64, ctypes.POINTER(ctypes.c_size_t)],
         "sclmlp_create": [I64, P, ctypes.c_size_t, P, ctypes.POINTER(P)],
         "sclmlp_destroy": [P],
@@ -335,6 +339,31 @@ def sclbm_set_launch(ctx, tile_rows: int, zchunk: int, tile_waves: int = 1):
     _check(_lib.sclbm_set_launch(ctx, int(tile_rows), int(zchunk), int(tile_waves)))
 
 
+def sclbm_reset_launch(ctx):
+    """Back to the launch the context started with."""
+    _check(_lib.sclbm_reset_launch(ctx))
+
+
+TILES = ("fixed", "fitted", "planes")
+
+
+def _tiles(call, arg):
+    v = [ctypes.c_int32() for _ in range(5)]
+    _check(call(arg, *(ctypes.byref(x) for x in v)))
+    return {"kind": TILES[v[0].value], "width": v[1].value, "rows": v[2].value, "zchunk": v[3].value,
+            "cached": bool(v[4].value)}
+
+
+def sclbm_get_tiles(ctx) -> dict:
+    """What the context's steps run: kind, width, rows, zchunk, cached stores."""
+    return _tiles(_lib.sclbm_get_tiles, ctx)
+
+
+def sclbm_default_tiles(cfg: sclbm_config) -> dict:
+    """... and those of a context with this configuration at its start (host only)."""
+    return _tiles(_lib.sclbm_default_tiles, ctypes.byref(cfg))
+
+
 def sclbm_get_launch(ctx):
     """Returns (tile_rows, zchunk, tile_waves)."""
     t = ctypes.c_int32()
@@ -485,11 +514,16 @@ class Lattice:
                 table = {}
         if key in table:
             ty, zc, wx = table[key]["tile_rows"], table[key]["zchunk"], table[key]["tile_waves"]
-            self.set_launch(ty, zc, wx)
+            if table[key]["start"]:
+                self.reset_launch()
+            else:
+                self.set_launch(ty, zc, wx)
             return ty, zc, wx, table[key]["ms"]
         ty, zc, wx, ms = sclbm_autotune(self.ctx, trial_steps)
         if cache:
-            table[key] = {"tile_rows": ty, "zchunk": zc, "tile_waves": wx, "ms": ms}
+            # the start's launch is not always the shape it is reported as
+            start = sclbm_get_tiles(self.ctx) == sclbm_default_tiles(self.cfg)
+            table[key] = {"tile_rows": ty, "zchunk": zc, "tile_waves": wx, "start": start, "ms": ms}
             try:
                 os.makedirs(os.path.dirname(path), exist_ok=True)
                 with open(path, "w") as fh:
@@ -569,8 +603,15 @@ class Lattice:
     def set_launch(self, tile_rows, zchunk, tile_waves=1):
         """Step-kernel tile of tile_rows rows x tile_waves 64-node columns and
         z-chunk of zchunk planes; (tile_rows, tile_waves) in (4, 1), (8, 1), (4, 2).
-        Speed only: results are bitwise the same for every shape."""
+        Speed only: results are bitwise the same for every shape.  The shape runs as
+        it is named, also where it is the default one (reset_launch returns to the start)."""
         sclbm_set_launch(self.ctx, tile_rows, zchunk, tile_waves)
+
+    def reset_launch(self):
+        sclbm_reset_launch(self.ctx)
+
+    def get_tiles(self) -> dict:
+        return sclbm_get_tiles(self.ctx)
 
     def get_launch(self):
         return sclbm_get_launch(self.ctx)

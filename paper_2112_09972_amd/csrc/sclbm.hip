@@ -3,7 +3,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -151,6 +150,14 @@ struct SmallShape {
     int planes = 0, waves = 0;
 };
 
+// What a step runs: kind (SCLBM_TILES_*), a tile's width and rows, planes per chunk, wavefronts per tile row of
+// fixed tiles, the store policy, and the shape of planes at once.
+struct StepTiles {
+    int kind = SCLBM_TILES_FIXED, w = 0, h = 0, zc = 0, waves = 0;
+    bool cached = false;
+    SmallShape small;
+};
+
 struct sclbm_ctx {
     sclbm_config cfg;
     Layout lay;
@@ -158,12 +165,13 @@ struct sclbm_ctx {
     hipStream_t stream;
     int64_t n;        // time of the state
     int par;          // which population buffer holds f(n): 0 -> f0
+    // the launch shape: the default one, of which the step makes `start`, or (named) one set by the caller
+    // or the autotuner, which runs as it is with streaming stores
     int tile_rows;    // TY
     int tile_waves;   // WX: wavefronts per tile row (tile width 64 WX)
     int zchunk;
-    int def_rows = 0, def_waves = 0, def_zc = 0;  // the default launch shape
-    SmallShape small;                             // ... as chunks of one or two planes at once (planes = 0: not)
-    int fit_w = 0, fit_h = 0, fit_zc = 0;         // fitted tiles that run in its place (0: none)
+    bool named = false;
+    StepTiles start;
     std::vector<int64_t> tab_first, tab_len;  // host copies, per box
     // captured step loop: valid for (graph_steps, graph_par, graph_ty, graph_wx, graph_zc)
     hipGraphExec_t graph_exec = nullptr;
@@ -187,6 +195,15 @@ struct sclbm_ctx {
     // One FP64 value per node of every box, between steps: the population buffer that does not hold
     // the state, which the next step writes in full (76 bytes a node or more).
     double *scratch_field() { return reinterpret_cast<double *>(fbuf(1 - par)); }
+    StepTiles tiles() const {
+        if (!named) return start;
+        StepTiles t;
+        t.w = 64 * tile_waves;
+        t.h = tile_rows;
+        t.zc = zchunk;
+        t.waves = tile_waves;
+        return t;
+    }
     double *diag() { return reinterpret_cast<double *>(ws + lay.diag); }
     int64_t *clock() { return reinterpret_cast<int64_t *>(ws + lay.clock); }
 };
@@ -433,30 +450,70 @@ hipError_t launch_step_planes(sclbm_ctx *c, const StepArgs &a) {
     return hipGetLastError();
 }
 template <int P>
-hipError_t launch_step_small(sclbm_ctx *c, const StepArgs &a) {
-    if (c->small.planes == 3) return launch_step_planes<P, 3, 2>(c, a);
-    if (c->small.waves == 2) return launch_step_planes<P, 4, 2>(c, a);
+hipError_t launch_step_small(sclbm_ctx *c, const StepArgs &a, const SmallShape &s) {
+    if (s.planes == 3) return launch_step_planes<P, 3, 2>(c, a);
+    if (s.waves == 2) return launch_step_planes<P, 4, 2>(c, a);
     return launch_step_planes<P, 4, widest_small(P)>(c, a);
 }
 
 template <int P, int ST>
-hipError_t launch_step_st(sclbm_ctx *c, const StepArgs &a) {
+hipError_t launch_step_st(sclbm_ctx *c, const StepArgs &a, const StepTiles &t) {
     if constexpr (P != SCLBM_F32D) {  // (no fitted march: default_fit)
-        if (a.tile_w) return launch_step_tile<P, 0, FIT_WAVES, ST>(c, a);
+        if (t.kind == SCLBM_TILES_FITTED) return launch_step_tile<P, 0, FIT_WAVES, ST>(c, a);
     }
     if constexpr (Prec<P>::DEV) {
-        if (c->tile_waves == 4) return launch_step_tile<P, 4, 4, ST>(c, a);
+        if (t.waves == 4) return launch_step_tile<P, 4, 4, ST>(c, a);
     }
-    if (c->tile_waves == 2) return launch_step_tile<P, 4, 2, ST>(c, a);
-    if (c->tile_rows == 8) return launch_step_tile<P, 8, 1, ST>(c, a);
+    if (t.waves == 2) return launch_step_tile<P, 4, 2, ST>(c, a);
+    if (t.h == 8) return launch_step_tile<P, 8, 1, ST>(c, a);
     return launch_step_tile<P, 4, 1, ST>(c, a);
 }
 
 template <int P>
 hipError_t launch_step(sclbm_ctx *c, const StepArgs &a) {
-    if (a.tile_w && c->small.planes) return launch_step_small<P>(c, a);
-    const int w = a.tile_w ? a.tile_w : 64 * c->tile_waves;
-    return cached_stores(c->cfg, w, a.tile_w != 0) ? launch_step_st<P, kStoreCached>(c, a) : launch_step_st<P, kStoreNT>(c, a);
+    const StepTiles t = c->tiles();
+    if (t.kind == SCLBM_TILES_PLANES) return launch_step_small<P>(c, a, t.small);
+    return t.cached ? launch_step_st<P, kStoreCached>(c, a, t) : launch_step_st<P, kStoreNT>(c, a, t);
+}
+
+// The tiles of the default launch shape.
+StepTiles default_tiles(const sclbm_config &c) {
+    StepTiles t;
+    default_tile(c, t.h, t.waves);
+    t.w = 64 * t.waves;
+    t.zc = default_zchunk(c, t.h, t.waves);
+    int w, h, zc;
+    t.small = small_tiles(c, w, h);
+    if (t.small.planes) {
+        t.kind = SCLBM_TILES_PLANES;
+        zc = t.small.planes - 2;
+    } else {
+        default_fit(c, w, h, zc);
+        if (w) t.kind = SCLBM_TILES_FITTED;
+    }
+    if (t.kind != SCLBM_TILES_FIXED) {
+        t.w = w;
+        t.h = h;
+        t.zc = zc;
+        t.waves = 0;
+    }
+    t.cached = t.kind != SCLBM_TILES_PLANES && cached_stores(c, t.w, t.kind == SCLBM_TILES_FITTED);
+    return t;
+}
+
+void put_tiles(const StepTiles &t, int32_t *kind, int32_t *width, int32_t *rows, int32_t *zchunk, int32_t *cached) {
+    if (kind) *kind = t.kind;
+    if (width) *width = t.w;
+    if (rows) *rows = t.h;
+    if (zchunk) *zchunk = t.zc;
+    if (cached) *cached = t.cached;
+}
+
+// The context's launch shape back to the default.
+void default_shape(sclbm_ctx *c) {
+    default_tile(c->cfg, c->tile_rows, c->tile_waves);
+    c->zchunk = default_zchunk(c->cfg, c->tile_rows, c->tile_waves);
+    c->named = false;
 }
 
 hipError_t launch_step_prec(sclbm_ctx *c, const StepArgs &a) {
@@ -673,6 +730,14 @@ sclbm_status sclbm_default_launch(const sclbm_config *cfg, int32_t *tile_rows, i
     return SCLBM_OK;
 }
 
+sclbm_status sclbm_default_tiles(const sclbm_config *cfg, int32_t *kind, int32_t *width, int32_t *rows, int32_t *zchunk,
+                                 int32_t *cached) {
+    std::string why;
+    if (!config_ok(cfg, why)) return fail(SCLBM_EINVAL, "invalid config: %s", why.c_str());
+    put_tiles(default_tiles(*cfg), kind, width, rows, zchunk, cached);
+    return SCLBM_OK;
+}
+
 sclbm_status sclbm_create(const sclbm_config *cfg, void *dev_workspace, size_t bytes, void *hip_stream,
                           sclbm_ctx **out) {
     std::string why;
@@ -702,14 +767,8 @@ sclbm_status sclbm_create(const sclbm_config *cfg, void *dev_workspace, size_t b
     c->stream = static_cast<hipStream_t>(hip_stream);
     c->n = 0;
     c->par = 0;
-    default_tile(*cfg, c->tile_rows, c->tile_waves);
-    c->zchunk = default_zchunk(*cfg, c->tile_rows, c->tile_waves);
-    c->def_rows = c->tile_rows;
-    c->def_waves = c->tile_waves;
-    c->def_zc = c->zchunk;
-    c->small = small_tiles(*cfg, c->fit_w, c->fit_h);
-    c->fit_zc = c->small.planes - 2;
-    if (!c->small.planes) default_fit(*cfg, c->fit_w, c->fit_h, c->fit_zc);
+    default_shape(c);
+    c->start = default_tiles(*cfg);
     c->tab_first.assign(cfg->nbox, 0);
     c->tab_len.assign(cfg->nbox, 0);
     c->N = int64_t(cfg->nx) * cfg->ny * cfg->nz;
@@ -878,10 +937,10 @@ StepArgs base_args(sclbm_ctx *c) {
     a.nx = c->cfg.nx;
     a.ny = c->cfg.ny;
     a.nz = c->cfg.nz;
-    const bool fit = c->fit_w > 0 && c->tile_rows == c->def_rows && c->tile_waves == c->def_waves && c->zchunk == c->def_zc;
-    a.tile_w = fit ? c->fit_w : 0;
-    a.tile_h = fit ? c->fit_h : 0;
-    a.zchunk = fit ? c->fit_zc : c->zchunk;
+    const StepTiles t = c->tiles();
+    a.tile_w = t.w;
+    a.tile_h = t.h;
+    a.zchunk = t.zc;
     a.nzc = (c->cfg.nz + a.zchunk - 1) / a.zchunk;
     // tile order: x fastest, then y, then z-chunk (groups of one chunk).  Each XCD
     // then takes a run of neighbouring rows of one chunk, whose ring rows it reads
@@ -989,19 +1048,28 @@ sclbm_status sclbm_autotune(sclbm_ctx *c, int32_t trial_steps, int32_t *tile_row
     if (trial_steps < 1 || trial_steps > 100000) return fail(SCLBM_EINVAL, "trial_steps must be in [1, 100000]");
     if ((st = check_table(c, int64_t(trial_steps) + 1))) return st;
     const int ty_keep = c->tile_rows, wx_keep = c->tile_waves, zc_keep = c->zchunk;
+    const bool named_keep = c->named;
     const int64_t n0 = c->n;
     const int par0 = c->par;
     hipEvent_t ev0, ev1;
     HIP_TRY(hipEventCreate(&ev0));
     HIP_TRY(hipEventCreate(&ev1));
     float best = -1.0f;
-    int bty = ty_keep, bwx = wx_keep, bzc = zc_keep;
-    // candidates: every valid tile with z-chunks 2 .. 64 (capped at nz), the
-    // tile's default z-chunk, so that the default launch is always among them,
-    // and the chunk that fills the device in one round
+    // candidates: the default launch (with what the step makes of it), then every valid
+    // tile with z-chunks 2 .. 64 (capped at nz), the tile's default z-chunk and the
+    // chunk that fills the device in one round, as named shapes
     const int tys[4] = {4, 8, 4, 4}, wxs[4] = {1, 1, 2, 4};
     const int zcs[6] = {2, 4, 8, 16, 32, 64};
-    std::vector<std::array<int, 3>> cand;
+    struct Candidate {
+        int ty, wx, zc;
+        bool named;
+    };
+    std::vector<Candidate> cand;
+    default_shape(c);
+    const Candidate start{c->tile_rows, c->tile_waves, c->zchunk, false};
+    const bool plain = c->start.kind == SCLBM_TILES_FIXED && !c->start.cached;  // the same launch as the shape named
+    cand.push_back(start);
+    Candidate bc = start;
     for (int ti = 0; ti < 4; ++ti) {
         if (!valid_tile(c->cfg, tys[ti], wxs[ti])) continue;
         if (c->cfg.nx <= 64 * (wxs[ti] / 2)) continue;  // the tile's last column would hold no nodes
@@ -1011,13 +1079,16 @@ sclbm_status sclbm_autotune(sclbm_ctx *c, int32_t trial_steps, int32_t *tile_row
         if (const int z1 = one_round_zchunk(c->cfg, tys[ti], wxs[ti])) zl.push_back(z1);
         std::sort(zl.begin(), zl.end());
         zl.erase(std::unique(zl.begin(), zl.end()), zl.end());
-        for (int zc : zl) cand.push_back({tys[ti], wxs[ti], zc});
+        for (int zc : zl)
+            if (!(plain && tys[ti] == start.ty && wxs[ti] == start.wx && zc == start.zc))
+                cand.push_back({tys[ti], wxs[ti], zc, true});
     }
     sclbm_status result = SCLBM_OK;
     for (size_t ci = 0; ci < cand.size() && result == SCLBM_OK; ++ci) {
-        c->tile_rows = cand[ci][0];
-        c->tile_waves = cand[ci][1];
-        c->zchunk = cand[ci][2];
+        c->tile_rows = cand[ci].ty;
+        c->tile_waves = cand[ci].wx;
+        c->zchunk = cand[ci].zc;
+        c->named = cand[ci].named;
         int64_t clk[2] = {n0, n0};
         hipError_t e = hipMemcpyAsync(c->clock(), clk, sizeof clk, hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) e = enqueue_steps(c, 1, par0 ^ 0);  // warm-up (reads row n0)
@@ -1035,9 +1106,7 @@ sclbm_status sclbm_autotune(sclbm_ctx *c, int32_t trial_steps, int32_t *tile_row
         ms /= float(trial_steps);
         if (best < 0.0f || ms < best) {
             best = ms;
-            bty = c->tile_rows;
-            bwx = c->tile_waves;
-            bzc = c->zchunk;
+            bc = cand[ci];
         }
     }
     (void)hipEventDestroy(ev0);  // teardown: nothing to do on failure
@@ -1052,15 +1121,17 @@ sclbm_status sclbm_autotune(sclbm_ctx *c, int32_t trial_steps, int32_t *tile_row
         c->tile_rows = ty_keep;
         c->tile_waves = wx_keep;
         c->zchunk = zc_keep;
+        c->named = named_keep;
         return result;
     }
-    c->tile_rows = bty;
-    c->tile_waves = bwx;
-    c->zchunk = bzc;
+    c->tile_rows = bc.ty;
+    c->tile_waves = bc.wx;
+    c->zchunk = bc.zc;
+    c->named = bc.named;
     drop_graph(c);
-    if (tile_rows) *tile_rows = bty;
-    if (zchunk) *zchunk = bzc;
-    if (tile_waves) *tile_waves = bwx;
+    if (tile_rows) *tile_rows = bc.ty;
+    if (zchunk) *zchunk = bc.zc;
+    if (tile_waves) *tile_waves = bc.wx;
     if (best_ms) *best_ms = best;
     return SCLBM_OK;
 }
@@ -1387,7 +1458,24 @@ sclbm_status sclbm_set_launch(sclbm_ctx *c, int32_t tile_rows, int32_t zchunk, i
     c->tile_rows = tile_rows;
     c->tile_waves = tile_waves;
     c->zchunk = std::min<int32_t>(zchunk, c->cfg.nz);
+    c->named = true;
     drop_graph(c);
+    return SCLBM_OK;
+}
+
+sclbm_status sclbm_reset_launch(sclbm_ctx *c) {
+    sclbm_status st = check_ctx(c);
+    if (st) return st;
+    default_shape(c);
+    drop_graph(c);
+    return SCLBM_OK;
+}
+
+sclbm_status sclbm_get_tiles(const sclbm_ctx *c, int32_t *kind, int32_t *width, int32_t *rows, int32_t *zchunk,
+                             int32_t *cached) {
+    sclbm_status st = check_ctx(c);
+    if (st) return st;
+    put_tiles(c->tiles(), kind, width, rows, zchunk, cached);
     return SCLBM_OK;
 }
 

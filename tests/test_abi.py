@@ -180,3 +180,27 @@ def test_lane_exchanges_through_lds_are_fenced():
         users[name] = (text.count("__builtin_amdgcn_wave_barrier"), text.count("__builtin_amdgcn_fence"))
     assert users.pop("wave.hpp") == (1, 2)
     assert all(n == (0, 0) for n in users.values()), users
+
+
+@pytest.mark.parametrize("n,nbox,prec,expect", [
+    ((32, 32, 32), 1, "f64", ("planes", 32, 4, 1, False)), ((40, 57, 33), 1, "f64", ("planes", 40, 4, 2, False)),
+    ((128, 128, 128), 1, "f32", ("fixed", 128, 4, 16, False)), ((64, 64, 64), 64, "f32", ("fixed", 64, 8, 64, False)),
+    ((256, 256, 256), 1, "f16dev", ("fixed", 256, 4, 64, False)),
+    ((150, 93, 67), 1, "bf16dev", ("fitted", 50, 10, 4, True)), ((100, 120, 90), 1, "f64", ("fitted", 100, 5, 9, False)),
+    ((150, 40, 90), 1, "f32d", ("fixed", 64, 8, 6, True))])
+def test_default_tiles_of_known_boxes(n, nbox, prec, expect):
+    """What a context starts with, computed without a device: the three kinds of tiles and both
+    store policies; a fixed default is the shape sclbm_default_launch reports."""
+    import paper_2112_09972_amd as sc
+    c = cfg(nx=n[0], ny=n[1], nz=n[2], nbox=nbox, prec=sc.PREC[prec])
+    t = sc.sclbm_default_tiles(c)
+    assert tuple(t.values()) == expect
+    if t["kind"] == "fixed":
+        ty, zc, wx = sc.sclbm_default_launch(c)
+        assert (t["width"], t["rows"], t["zchunk"]) == (64 * wx, ty, zc)
+    with pytest.raises(sc.SclbmError):
+        sc.sclbm_default_tiles(cfg(nx=2))
+    with pytest.raises(sc.SclbmError):
+        sc.sclbm_get_tiles(None)
+    with pytest.raises(sc.SclbmError):
+        sc.sclbm_reset_launch(None)

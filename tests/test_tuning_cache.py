@@ -27,6 +27,10 @@ def lat(monkeypatch, tmp_path):
 
     monkeypatch.setattr(sc, "sclbm_autotune", tune)
     monkeypatch.setattr(sc, "sclbm_set_launch", lambda ctx, *shape: o.calls.append(shape))
+    monkeypatch.setattr(sc, "sclbm_reset_launch", lambda ctx: o.calls.append("reset"))
+    monkeypatch.setattr(sc, "sclbm_get_tiles", lambda ctx: o.tiles)
+    monkeypatch.setattr(sc, "sclbm_default_tiles", lambda cfg: {"kind": "planes"})
+    o.tiles = {"kind": "fixed"}
     return o, lib, tmp_path / "cache" / "sclbm" / "tuning.json"
 
 
@@ -50,3 +54,15 @@ def test_result_of_an_earlier_build_is_not_used(lat):
     assert o.autotune() == (4, 8, 1, 0.5)
     assert "tune" in o.calls
     assert stale.items() <= json.loads(path.read_text()).items()
+
+
+@pytest.mark.parametrize("kind,expect", [("planes", "reset"), ("fixed", (4, 8, 1))])
+def test_the_start_is_set_again_as_the_start(lat, kind, expect):
+    """Where the launch a context starts with won, a cached result brings that launch back
+    and not the shape it is reported as."""
+    o, _, _ = lat
+    o.tiles = {"kind": kind}
+    o.autotune()
+    assert o.calls == ["tune"]
+    assert o.autotune() == (4, 8, 1, 0.5)
+    assert o.calls == ["tune", expect]
