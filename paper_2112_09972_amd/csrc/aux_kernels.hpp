@@ -182,39 +182,42 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[K], double *out /
 // FP32) and 1322 us (256^3 FP16).
 // The items (x tile, y tile, z-chunk) of a workgroup are consecutive, and the workgroups of
 // one XCD next to one another, so that rings and chunk ends hit in its L2.
-constexpr int VEL_TX = 64, VEL_TY = 8, VEL_THREADS = VEL_TX * VEL_TY;
+// Boxes at most 8 nodes wide take tiles of 8 x 64 (TX = 8), or of 8 x 8 in one wavefront (NT = 64) where
+// y is as short: 64 x 8 would leave most lanes idle (densities and velocity, FP32: 3 x 300 x 300 59 -> 28 us,
+// 5 x 512 x 512 150 -> 71, 3 x 3 x 20000 62 -> 25; gathering from global memory 50, 163 and 34).
 constexpr int VEL_BLOCKS = 2048;  // most workgroups of a launch
-constexpr int VEL_RING = 2 * (VEL_TX + 2) + 2 * VEL_TY;
-template <bool E0>
-__global__ __launch_bounds__(VEL_THREADS) void k_velocity(BoxGeom g, const double *rho_a, const double *rho_b, int ghost,
+template <bool E0, int TX, int NT>
+__global__ __launch_bounds__(NT) void k_velocity(BoxGeom g, const double *rho_a, const double *rho_b, int ghost,
                                                           double gab, double rb0, double rb1, double *u, int zchunk,
                                                           Mat3 A, double *partial) {
-    __shared__ double ld[2][2][VEL_TY + 2][VEL_TX + 2];
-    const int ntx = (g.nx + VEL_TX - 1) / VEL_TX, nty = (g.ny + VEL_TY - 1) / VEL_TY;
+    constexpr int TY = NT / TX, RING = 2 * (TX + 2) + 2 * TY;
+    static_assert(RING <= NT, "one ring node per thread");
+    __shared__ double ld[2][2][TY + 2][TX + 2];
+    const int ntx = (g.nx + TX - 1) / TX, nty = (g.ny + TY - 1) / TY;
     const uint32_t nitem = uint32_t(ntx) * uint32_t(nty) * uint32_t((g.nz + zchunk - 1) / zchunk);
     const uint32_t q8 = gridDim.x / 8, r8 = gridDim.x % 8, xcd = blockIdx.x % 8, k8 = blockIdx.x / 8;
     const uint32_t blk = xcd < r8 ? xcd * (q8 + 1) + k8 : r8 * (q8 + 1) + (xcd - r8) * q8 + k8;
     const uint32_t first = uint32_t(uint64_t(blk) * nitem / gridDim.x);
     const uint32_t last = uint32_t(uint64_t(blk + 1) * nitem / gridDim.x);
     const uint32_t nxy = uint32_t(g.nx) * uint32_t(g.ny);
-    const int tid = threadIdx.x, lx = tid & 63, ly = tid >> 6;
+    const int tid = threadIdx.x, lx = tid % TX, ly = tid / TX;
     const double rbnd[2] = {rb0, rb1};
     double v[2] = {0.0, 0.0};
     for (uint32_t item = first; item < last; ++item) {
-        const int x0 = int(item % uint32_t(ntx)) * VEL_TX, y0 = int(item / uint32_t(ntx) % uint32_t(nty)) * VEL_TY;
+        const int x0 = int(item % uint32_t(ntx)) * TX, y0 = int(item / uint32_t(ntx) % uint32_t(nty)) * TY;
         const int zs = int(item / uint32_t(ntx) / uint32_t(nty)) * zchunk, ze = min(zs + zchunk, g.nz);
         const int x = x0 + lx, y = y0 + ly;
         const bool valid = x < g.nx && y < g.ny;
-        // the ring node of this thread: rows y0 - 1 and y0 + VEL_TY, then columns x0 - 1 and x0 + VEL_TX
-        const bool ring_on = tid < VEL_RING;
+        // the ring node of this thread: rows y0 - 1 and y0 + TY, then columns x0 - 1 and x0 + TX
+        const bool ring_on = tid < RING;
         int rx, ry;
-        if (tid < 2 * (VEL_TX + 2)) {
-            ry = tid < VEL_TX + 2 ? 0 : VEL_TY + 1;
-            rx = tid < VEL_TX + 2 ? tid : tid - (VEL_TX + 2);
+        if (tid < 2 * (TX + 2)) {
+            ry = tid < TX + 2 ? 0 : TY + 1;
+            rx = tid < TX + 2 ? tid : tid - (TX + 2);
         } else {
-            const int r = tid - 2 * (VEL_TX + 2);
-            rx = r < VEL_TY ? 0 : VEL_TX + 1;
-            ry = 1 + (r < VEL_TY ? r : r - VEL_TY);
+            const int r = tid - 2 * (TX + 2);
+            rx = r < TY ? 0 : TX + 1;
+            ry = 1 + (r < TY ? r : r - TY);
         }
         // offset of a (x, y) in its plane after the wrap; false where it is a ghost or lies beyond
         // the one node past the box that a valid node's stencil reaches
@@ -258,7 +261,7 @@ __global__ __launch_bounds__(VEL_THREADS) void k_velocity(BoxGeom g, const doubl
         Plane p0{}, p1{};  // planes z - 2 and z - 1
         load(zs - 1);
         for (int z = zs - 1; z <= ze; ++z) {
-            double(*const pl)[VEL_TY + 2][VEL_TX + 2] = ld[(z - zs + 1) & 1];
+            double(*const pl)[TY + 2][TX + 2] = ld[(z - zs + 1) & 1];
             pl[0][ly + 1][lx + 1] = own[0];
             pl[1][ly + 1][lx + 1] = own[1];
             if (ring_on) {
@@ -323,7 +326,7 @@ __global__ __launch_bounds__(VEL_THREADS) void k_velocity(BoxGeom g, const doubl
         }
         __syncthreads();  // the next item writes the buffer the last plane was read from
     }
-    if constexpr (E0) block_reduce_store<2, VEL_THREADS>(v, partial + (int64_t)blk * 2);
+    if constexpr (E0) block_reduce_store<2, NT>(v, partial + (int64_t)blk * 2);
 }
 
 // Per-workgroup partials of: mass A, mass B, momentum (3), indicator moments

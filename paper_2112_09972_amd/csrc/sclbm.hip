@@ -679,27 +679,29 @@ sclbm_status launch_density(sclbm_ctx *c, int32_t box, double *ra, double *rb, d
     return SCLBM_OK;
 }
 
-// Launch of k_velocity: z-chunks long enough that the two planes read beyond each cost
-// little, but about four workgroups per CU where the box has the planes for it (at least 4 a
-// chunk); at most VEL_BLOCKS workgroups, so that their E0 partials fit the workspace's (at
-// least NRED_BLOCKS x NSTAT values).
-static_assert(VEL_BLOCKS * 2 <= NRED_BLOCKS * NSTAT, "E0 partials");
-void velocity_launch(const sclbm_ctx *c, int &zchunk, int &blocks) {
-    const int64_t tiles = int64_t((c->cfg.nx + VEL_TX - 1) / VEL_TX) * ((c->cfg.ny + VEL_TY - 1) / VEL_TY);
-    const int64_t want = std::min<int64_t>((1024 + tiles - 1) / tiles, std::max(1, c->cfg.nz / 4));
-    zchunk = int((c->cfg.nz + want - 1) / want);
-    blocks = int(std::min<int64_t>(tiles * ((c->cfg.nz + zchunk - 1) / zchunk), VEL_BLOCKS));
-}
-
 // Velocity of a box from ra, rb and the momenta in u (overwritten), or with E0 the error
-// sums against the flow A in c->partial().
+// sums against the flow A in c->partial().  Z-chunks long enough that the two planes read
+// beyond each cost little, but about four workgroups per CU where the box has the planes for
+// it (at least 4 a chunk; eight workgroups of one wavefront); at most VEL_BLOCKS workgroups, so that
+// their E0 partials fit the workspace's (at least NRED_BLOCKS x NSTAT values).
+static_assert(VEL_BLOCKS * 2 <= NRED_BLOCKS * NSTAT, "E0 partials");
 template <bool E0>
 sclbm_status launch_velocity(sclbm_ctx *c, const double *ra, const double *rb, double *u, const Mat3 &A,
                              int *nblocks = nullptr) {
-    int zchunk, blocks;
-    velocity_launch(c, zchunk, blocks);
-    k_velocity<E0><<<blocks, VEL_THREADS, 0, c->stream>>>(c->geom, ra, rb, int(c->cfg.bc == SCLBM_BC_GHOST), c->cfg.g_ab,
-                                                         c->cfg.rho_b[0], c->cfg.rho_b[1], u, zchunk, A, c->partial());
+    int blocks = 0;
+    auto run = [&](auto kernel, int tx, int threads) {
+        const int ty = threads / tx;
+        const int64_t tiles = int64_t((c->cfg.nx + tx - 1) / tx) * ((c->cfg.ny + ty - 1) / ty);
+        const int64_t all = threads == 64 ? VEL_BLOCKS : VEL_BLOCKS / 2;
+        const int64_t want = std::min<int64_t>((all + tiles - 1) / tiles, std::max(1, c->cfg.nz / 4));
+        const int zchunk = int((c->cfg.nz + want - 1) / want);
+        blocks = int(std::min<int64_t>(tiles * ((c->cfg.nz + zchunk - 1) / zchunk), VEL_BLOCKS));
+        kernel<<<blocks, threads, 0, c->stream>>>(c->geom, ra, rb, int(c->cfg.bc == SCLBM_BC_GHOST), c->cfg.g_ab,
+                                                  c->cfg.rho_b[0], c->cfg.rho_b[1], u, zchunk, A, c->partial());
+    };
+    if (c->cfg.nx > 8) run(k_velocity<E0, 64, 512>, 64, 512);
+    else if (c->cfg.ny > 8) run(k_velocity<E0, 8, 512>, 8, 512);
+    else run(k_velocity<E0, 8, 64>, 8, 64);
     HIP_LAUNCHED();
     if (nblocks) *nblocks = blocks;
     return SCLBM_OK;

@@ -172,3 +172,30 @@ def test_surface_of_several_ragged_boxes_between_steps(sc, nxyz, nbox, prec):
         lat.step(steps)
         plain.step(steps)
         assert np.array_equal(lat.save(), plain.save())
+
+
+@pytest.mark.parametrize("bc", ["ghost", "periodic"])
+@pytest.mark.parametrize("prec,nxyz", [(p, n) for p in ("f64", "f16dev") for n in (
+    (3, 4, 60), (8, 8, 7), (8, 9, 6), (5, 64, 5), (8, 65, 9), (3, 130, 4), (9, 8, 11), (9, 9, 4), (64, 17, 9), (70, 16, 5))]
+    + [("f32", (4096, 264, 3))])
+def test_velocity_tiles_and_items(sc, nxyz, prec, bc):
+    """The velocity pass's three tilings (8 x 8 and 8 x 64 for boxes up to eight nodes wide,
+    64 x 8) at the edges of their tiles, full last rows and one node past them, and a
+    box of more tiles than workgroups (2112, so that workgroups take a second one).
+    Bounds as for the ragged boxes above."""
+    nx, ny, nz = nxyz
+    rng = np.random.default_rng(nx * 7 + ny)
+    ra = rng.uniform(0.2, 1.0, (nz, ny, nx))
+    rb = rng.uniform(0.2, 1.0, (nz, ny, nx))
+    u = 0.05 * rng.standard_normal((3, nz, ny, nx))
+    A = np.array([[1e-3, 2e-3, 0], [0, -4e-3, 1e-3], [3e-3, 0, 3e-3]])
+    lat = sc.Lattice(nx, ny, nz, bc=bc, prec=prec, table_len=1, g_ab=wl.G_AB, rho_b=(0.05, 1.0))
+    o = oracle.Oracle(nx, ny, nz, periodic=bc == "periodic", g=wl.G_AB, rho_b=(0.05, 1.0))
+    lat.init_fields(ra, rb, u)
+    o.init_fields(ra, rb, u)
+    got = [t.cpu().numpy() for t in lat.fields()]
+    ref = o.fields()
+    tol = {"f64": 1e-14, "f32": 2.0 ** -22, "f16dev": 2.0 ** -10}[prec]
+    for g, r in zip(got, ref):
+        assert np.abs(g - r).max() <= tol * max(1.0, np.abs(r).max())
+    assert lat.velocity_error(A.reshape(9)) == pytest.approx(oracle.velocity_error(got[2], A.reshape(9), o.xc), rel=1e-12)
