@@ -335,3 +335,46 @@ def test_threads_share_a_network_from_their_own_streams(env):
         assert len(got[i]) == 25
         for k in range(25):
             assert torch.equal(got[i][k], want[i][k]), (i, k)
+
+
+def gradients_and_fused_step(env, n, max_batch):
+    """Gradients of n gathered rows against the FP64 reference with the same storage (bounds
+    of the file's head), then training steps equal, bit for bit, to the gradients
+    followed by Adam, symmetries included."""
+    torch, mlp = env
+    rng = np.random.default_rng(n)
+    w, t = make_batch(40 + n, 700)
+    idx = rng.integers(0, 700, n).astype(np.int32)
+    dev = [torch.from_numpy(v).cuda() for v in (w, t, idx, np.zeros(n, np.int32))]
+    (net, p), (other, _) = [setup_net(torch, mlp, 20, max_batch=max_batch) for _ in range(2)]
+    loss = net.gradients(*dev).item()
+    tn = (t[idx].astype(np.float64) - OUT_SHIFT) * OUT_SCALE
+    l_ref, g_ref = ref.backward(rounded_params(p), w[idx].astype(np.float64), tn, round_hidden=ref.round_bf16,
+                                round_grad=ref.round_bf16)
+    assert loss == pytest.approx(l_ref, rel=5e-3)
+    check_grads(net.grads().astype(np.float64), g_ref, 2e-2, "n=%d of %d" % (n, max_batch))
+    dev[3] = torch.from_numpy(rng.integers(0, 48, n).astype(np.int32)).cuda()
+    for _ in range(2):
+        net.gradients(*dev)
+        net.adam(1e-3)
+        other.train_step(*dev, lr=1e-3)
+        assert np.array_equal(net.grads(), other.grads())
+        assert np.array_equal(net.params(), other.params())
+    assert net.gradients(*dev).item() == other.gradients(*dev).item()
+    assert np.array_equal(net.grads(), other.grads())
+
+
+@pytest.mark.parametrize("n", [2048, 2049, 3200, 4096, 4097, 6300, 8192, 9000])
+def test_large_batches(env, n):
+    """At the edges of the tilings (layers: 32 x 32 tiles up to 2048 rows, 64 x 32 up to 4096,
+    64 x 64 above; weight gradients: 64 x 64 in slices above 2048) and over the slice
+    counts: three and five with a shorter last one, four, seven with a shorter last
+    one, eight, and eight of more than 1024 rows."""
+    gradients_and_fused_step(env, n, n)
+
+
+@pytest.mark.parametrize("n", [1, 300, 2048, 2049, 4097])
+def test_small_batches_of_a_large_context(env, n):
+    """Workspace offsets and paddings belong to the context's largest batch, tiles and slices to the
+    batch in hand."""
+    gradients_and_fused_step(env, n, 9000)
