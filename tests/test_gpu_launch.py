@@ -89,3 +89,99 @@ def test_autotuner_and_cache_set_what_they_measured(sc, prec, nxyz, tmp_path, mo
         o.step(5)
     assert np.array_equal(other.save(), ref.save())
     assert np.array_equal(lat.save(), ref.save())
+
+
+# What a context starts with, by format: (box, boxes, kind, tiles in a row, cached stores).  Fitted tiles: rows held
+# whole (24 rows of a tile among them) and cut in two to seven, with a narrower last one; fixed tiles with cached
+# stores: each shape, rows held whole and cut; planes at once: chunks of one and two planes, odd counts
+# (a last chunk of one), rows held whole and cut in two to four, four wavefronts a plane.
+PLANES = [((3, 3, 3), 1, "planes", 1, False), ((32, 32, 32), 1, "planes", 1, False), ((68, 12, 12), 1, "planes", 2, False),
+          ((124, 12, 13), 1, "planes", 3, False), ((128, 13, 14), 1, "planes", 4, False), ((45, 33, 29), 1, "planes", 1, False),
+          ((103, 19, 13), 1, "planes", 2, False), ((134, 13, 13), 1, "planes", 3, False), ((202, 13, 13), 1, "planes", 4, False),
+          ((40, 57, 33), 1, "planes", 1, False), ((21, 70, 9), 5, "planes", 1, False)]
+F32X = [((272, 43, 13), 1, "fixed", 5, True), ((372, 34, 12), 1, "fixed", 3, True)]
+DEV = [((13, 118, 99), 2, "fitted", 1, True), ((13, 33, 104), 2, "fitted", 1, False), ((133, 14, 86), 2, "fitted", 2, True),
+       ((142, 17, 116), 1, "fitted", 2, False), ((263, 55, 21), 1, "fitted", 3, True), ((406, 13, 19), 1, "fitted", 4, False),
+       ((257, 17, 86), 1, "fitted", 5, True), ((406, 21, 26), 2, "fitted", 6, True),
+       ((143, 118, 18), 1, "fixed", 3, True), ((55, 48, 115), 1, "fixed", 1, True), ((337, 53, 17), 1, "fixed", 3, True),
+       ((124, 34, 24), 3, "fixed", 1, True), ((419, 27, 28), 1, "fixed", 2, True), ((181, 43, 39), 1, "fixed", 1, True),
+       ((48, 48, 47), 1, "planes", 1, False)]
+STARTS = {
+    "f64": PLANES + [((17, 93, 24), 2, "fitted", 1, True), ((13, 19, 62), 3, "fitted", 1, False),
+                     ((139, 18, 20), 3, "fitted", 2, True), ((277, 12, 22), 1, "fitted", 3, False),
+                     ((390, 13, 15), 1, "fitted", 4, True), ((413, 13, 20), 2, "fitted", 6, True),
+                     ((387, 51, 12), 1, "fitted", 7, True), ((154, 13, 38), 1, "fixed", 3, True),
+                     ((16, 26, 61), 3, "fixed", 1, True), ((209, 14, 26), 1, "fixed", 2, True),
+                     ((97, 22, 36), 1, "fixed", 1, True)],
+    "f32": PLANES + F32X + [((48, 48, 47), 1, "planes", 1, False), ((21, 77, 47), 2, "fitted", 1, True),
+                            ((12, 25, 92), 2, "fitted", 1, False), ((139, 25, 44), 1, "fitted", 2, True),
+                            ((266, 28, 13), 1, "fitted", 3, False), ((404, 28, 15), 1, "fitted", 4, True),
+                            ((412, 17, 28), 1, "fitted", 5, True), ((387, 51, 12), 1, "fitted", 7, True),
+                            ((55, 20, 69), 2, "fixed", 1, True), ((93, 17, 96), 1, "fixed", 1, True)],
+    "f32d": PLANES + F32X + [((15, 115, 64), 2, "fixed", 1, True), ((92, 40, 30), 2, "fixed", 1, True)],
+    "f16dev": PLANES + DEV,
+    "bf16dev": PLANES + DEV,
+}
+
+
+@pytest.mark.parametrize("bc", ["ghost", "periodic"])
+@pytest.mark.parametrize("prec,nxyz,nbox,kind,parts,cached", [(p,) + c for p in PRECS for c in STARTS[p]])
+def test_every_start_equals_a_march(sc, prec, nxyz, nbox, kind, parts, cached, bc):
+    """The launch a context starts with is the one meant, and gives the same bytes as 64 x 4
+    tiles in chunks of three planes after seven steps, of every box."""
+    lat, ref = (droplets(sc, nxyz, nbox, prec, bc) for _ in range(2))
+    t = lat.get_tiles()
+    assert (t["kind"], -(-nxyz[0] // t["width"]), t["cached"]) == (kind, parts, cached), t
+    ref.set_launch(4, 3, 1)
+    for o in (lat, ref):
+        o.step(7)
+    a, b = lat.save(), ref.save()
+    assert np.array_equal(a, b)
+    ra, rb = (v.cpu().numpy() for v in lat.fields(box=nbox - 1, velocity=False))
+    assert np.isfinite(ra).all() and np.isfinite(rb).all()
+
+
+def test_starts_with_the_nan_fill_build(sc):
+    """No fitted tile and no planes-at-once workgroup reads an LDS cell that none of its threads
+    wrote: with every cell NaN before each plane (libsclbm_debug.so) the states are the
+    same bytes (one process per build; the marches that are named: debug_fill_cases.py)."""
+    import json
+    import os
+    import subprocess
+    import sys
+    pkg = os.path.dirname(sc.__file__)
+    out = []
+    for lib in ("libsclbm.so", "libsclbm_debug.so"):
+        path = os.path.join(pkg, lib)
+        assert os.path.exists(path), "build() builds it"
+        env = dict(os.environ, SCLBM_LIBRARY=path, PYTHONPATH=os.path.dirname(pkg))
+        r = subprocess.run([sys.executable, os.path.abspath(__file__)], env=env, cwd=os.path.dirname(pkg),
+                           capture_output=True, text=True, timeout=100)
+        assert r.returncode == 0, r.stderr[-3000:]
+        out.append(json.loads(r.stdout.strip().splitlines()[-1]))
+    assert [o["library"].rsplit("/", 1)[1] for o in out] == ["libsclbm.so", "libsclbm_debug.so"]
+    assert len(out[0]["states"]) == sum(len(v) for v in STARTS.values()) * 2
+    assert out[0]["states"] == out[1]["states"]
+
+
+def main():
+    """States of every start with the library that SCLBM_LIBRARY names, as one JSON line."""
+    import hashlib
+    import json
+    import paper_2112_09972_amd as sc
+    states = {}
+    for prec in PRECS:
+        for nxyz, nbox, kind, _, _ in STARTS[prec]:
+            for bc in ("ghost", "periodic"):
+                lat = droplets(sc, nxyz, nbox, prec, bc)
+                assert lat.get_tiles()["kind"] == kind
+                lat.step(4)
+                m, _ = lat.totals(check=False)
+                assert np.isfinite(m).all()
+                states["%s %s %s" % (prec, nxyz, bc)] = hashlib.sha256(lat.save()[64:].tobytes()).hexdigest()[:16]
+                lat.close()
+    print(json.dumps({"library": sc.LIB_PATH, "states": states}))
+
+
+if __name__ == "__main__":
+    main()
