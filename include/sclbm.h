@@ -248,7 +248,9 @@ sclbm_status sclbm_velocity_error(sclbm_ctx *ctx, int32_t box, const double A[9]
  * and the volume of rho_A > rho_B, with phi = rho_A - rho_B taken linear inside
  * the six tetrahedra of every lattice cell (each cell split along its main
  * diagonal; the paper does not say how it measures the area).  dev_out:
- * [nbox][2] = {area, volume}, FP64 sums in a fixed order.  Enqueued. */
+ * [nbox][2] = {area, volume}, FP64 sums in a fixed order.  Enqueued.  Uses the
+ * population buffer that does not hold the state as scratch: in a captured graph
+ * replay it, like the steps, an even number of steps apart. */
 sclbm_status sclbm_droplet_surface_all(sclbm_ctx *ctx, double *dev_out);
 
 /* D_LBM of Sec. 5 Eq. 17 from an area and a volume (host arithmetic; area > 0, volume >= 0);
@@ -342,12 +344,13 @@ sclbm_status sclbm_autotune(sclbm_ctx *ctx, int32_t trial_steps, int32_t *tile_r
 sclbm_status sclbm_mm_semi_axes(const double *M, int64_t n, double *axes);
 
 /* Maffettone-Minale morphology tensor (Sec. 2 Eqs. 1, 2, 5) for ntraj
- * trajectories on the GPU, one thread each, FP64 classical RK4 with `substeps`
+ * trajectories on the GPU, FP64 classical RK4 with `substeps`
  * steps per table row and A(t) linear between rows; M = I is the sphere of the
  * reference radius.  dev_A: [ntraj][nrows][9] velocity gradients in table time
  * units; tau_d = eta_s R / sigma in the same units; chi the viscosity ratio;
  * dev_M0: [ntraj][9] initial tensors or NULL for I; dev_M: [ntraj][nrec][9] with
- * nrec = 1 + (nrows - 1) / record_every, record r at time r * record_every.
+ * nrec = 1 + (nrows - 1) / record_every, record r at time r * record_every; a
+ * record depends on no row after its own.
  * Needs no context; enqueues on hip_stream (NULL = null stream). */
 sclbm_status sclbm_mm_integrate(const double *dev_A, int64_t ntraj, int64_t nrows, double tau_d, double chi,
                                 int32_t substeps, int32_t record_every, const double *dev_M0, double *dev_M,

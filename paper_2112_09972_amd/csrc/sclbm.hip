@@ -394,8 +394,13 @@ SmallShape small_tiles(const sclbm_config &c, int &w, int &h) {
 // - Beyond it, rows of whole lines or halves of them stream (FP32 128^3 126, cached 134; 112 x 25 x 56 x 16 186, 197; FP64 96 x 125 x 90
 //   153, 165), and 256-wide 16-bit tiles (200^3 330, 341); other rows are cached (FP32 190^3 783 -> 623, 37 x 169 x 153 x 4
 //   462 -> 390).  In FP64: rows that tiles cut (150^3 658 -> 615); fitted tiles unless rows are whole 32-byte sectors
-//   (34 x 95 x 125 x 4 320 -> 272, 30 x 139 x 181 x 2 313 -> 259; 92 x 105 x 94 3 % slower); fixed ones for odd rows above 320 MB
-//   (57 x 146 x 198 x 2 537 -> 494; 111 x 41 x 163 124 -> 133).
+//   (34 x 95 x 125 x 4 320 -> 272, 30 x 139 x 181 x 2 313 -> 259; 92 x 105 x 94 3 % slower); fixed ones for odd rows above 320 MB,
+//   where one buffer alone exceeds the memory-side cache, which joins some of the parts before that (57 x 146 x 198 x 2
+//   537 -> 494; 11 boxes of 354 - 1345 MB 0.945 - 0.99 of the streaming time, six of 121 - 254 MB 1.00 - 1.06).
+// Over 894 boxes that the rules were not fitted to (1e5 to 9e6 nodes, all formats, both boundary modes, one to 16 boxes) a step
+// takes 0.890 of the time of fixed tiles with streaming stores and 1.007 of the best of {fitted, fixed} x {streaming, cached};
+// 29 are more than 3 % slower than the former (worst 9 %), 18 of them FP64 arithmetic on FP32 storage in ghost
+// mode on 128-wide tiles at 165 - 260 MB or with nx % 4 == 0, where the mean is 1.00 (single boxes 0.91 - 1.09).
 bool cached_stores(const sclbm_config &c, int w, bool fitted) {
     const bool cut = w < c.nx;
     if (state_bytes(c) <= double((c.prec == SCLBM_F32D && !cut ? 32 : 22) << 20)) return false;

@@ -52,11 +52,11 @@ sclbm_status fail(sclbm_status st, const char *fmt, ...) {
 constexpr size_t kAlign = 256;
 size_t round_up(size_t v, size_t a = kAlign) { return (v + a - 1) / a * a; }
 
-// Slices of the batch whose weight gradients are summed separately.  Up to 1024 rows 32 x 32
+// Slices of the batch whose weight gradients are summed separately.  Up to kSmallBatch rows 32 x 32
 // tiles give 800 wavefronts and need none; above, a wavefront takes 64 x 64 (half the operand
-// traffic) and the batch is cut into slices of about 1024 rows, at most 8, to have enough of them
-// (8192 rows: all gradients 30 us and their sum 5.5; one 64 x 64 tile per LDS-staging workgroup,
-// layer after layer, with the row sums after each, took 287).
+// traffic) and the batch is cut into slices of about 1024 rows, three at 2049 rows and at most 8, to
+// have enough of them (8192 rows: all gradients 30 us and their sum 5.5; one 64 x 64 tile per
+// LDS-staging workgroup, layer after layer, with the row sums after each, took 287).
 constexpr int64_t kSmallBatch = 2048;
 int grad_slices(int64_t mpad) { return mpad <= kSmallBatch ? 1 : int(std::min<int64_t>(8, (mpad + 1023) / 1024)); }
 
@@ -141,9 +141,9 @@ namespace {
 
 // One hidden layer over mpad rows: forward, or with MASK the gradient of the layer below.
 // Up to kSmallBatch rows a wavefront takes one 32 x 32 tile and a workgroup of its own (256 rows: 128
-// of them, 4.1 us a layer; 64 x 64 tiles staged through LDS, 32 workgroups, took 8.6); above,
-// 64 x 64, four to a workgroup, which reads each operand half as often (8192 rows: 11 us).
-
+// of them, 4.1 us a layer; 64 x 64 tiles staged through LDS, 32 workgroups, took 8.6).  Above, four
+// wavefronts to a workgroup: 64 x 32 each up to twice that, where 64 x 64 would leave fewer than a wavefront
+// per SIMD, then 64 x 64, which reads each operand half as often (8192 rows: 11 us).
 template <int K, bool MASK>
 sclbm_status layer(const sclmlp_ctx *c, const LayerArgs &g) {
     if (g.Mpad <= kSmallBatch)
