@@ -325,7 +325,11 @@ int row_bytes(const sclbm_config &c) { return c.nx * (is_dev(c.prec) ? 4 : int(e
 // 207 -> 238, 232 x 102 x 74 260 -> 308), or although one tile holds them (FP16 43 x 182 x 196 x 4 306 -> 360 in two);
 // narrow FP32 rows and 256-wide 16-bit tiles whose state streams from memory (FP32 43 x 174 x 48 x 16
 // 544 -> 580, periodic 31 x 87 x 27 x 16 114 -> 132, FP16 191 x 113 x 131 x 3 410 -> 444, where the fixed ones' wavefronts load whole lines);
-// FP64 arithmetic on FP32 storage, which spills with them.
+// FP64 arithmetic on FP32 storage, which spills with them; grids that fill little of a round, where the model counts one
+// round either way and the fitted tiles' workgroups, of more nodes, are the fewer.  Fitted time over fixed, below the line: rows in
+// several tiles, FP64 and FP32 with less than eight of them below 0.6 of a round 1.14 (19 boxes, 0.86 - 1.41; FP64 692 x 4 x 23
+// 20.1 -> 28.6), 16 bit below 0.45 1.05 (29 boxes, 0.90 - 1.22; BF16 268 x 5 x 15 x 8 21.8 -> 25.3), FP32 rows of 16 and more nodes
+// held whole below 0.45 0.97 - 1.18 (17 x 60 x 21 x 5 22.5 -> 26.5).  Above the lines 0.68 (767 boxes, 0.19 - 1.09).
 void default_fit(const sclbm_config &c, int &w, int &h, int &zc) {
     w = h = zc = 0;
     int ty, wx;
@@ -342,6 +346,10 @@ void default_fit(const sclbm_config &c, int &w, int &h, int &zc) {
         if (fh < 1) continue;
         const long tiles = long((c.nx + fw - 1) / fw) * long((c.ny + fh - 1) / fh) * c.nbox;
         const int z = best_zchunk(c, tiles, resident_groups(c, FIT_WAVES), cost);
+        double least = 0.0;  // of a round
+        if (ntx > 1) least = is_dev(c.prec) ? 0.45 : (c.ny < 8 ? 0.6 : 0.0);
+        else if (c.prec == SCLBM_F32 && c.nx >= 16) least = 0.45;
+        if (double(tiles * ((c.nz + z - 1) / z)) < least * double(resident_groups(c, FIT_WAVES))) continue;
         if (double(cost) * (1.0 + 0.1 * (ntx - 1)) > best) continue;
         best = std::nextafter(double(cost) * (1.0 + 0.1 * (ntx - 1)), 0.0);
         w = fw;
@@ -387,7 +395,8 @@ SmallShape small_tiles(const sclbm_config &c, int &w, int &h) {
 // itself; cached ones join them in the L2, at the price of rows that are read again.  Measured, us per step, streaming -> cached:
 // - Up to 22 MB of one buffer (the L2 caches hold 32 MB) nothing is gained and the writes wait for the end of
 //   the kernel: FP16 41 x 26 x 128 16.5 -> 17.5, BF16 143 x 26 x 36 periodic 14.5 -> 16.0; at 23 - 26 MB FP16 33 x 72 x 128
-//   26.7 -> 23.7, FP32 23 x 165 x 22 x 2 26.1 -> 21.5.  FP64 arithmetic on FP32 storage up to 32 MB, rows held whole (72 x 92 x 31
+//   26.7 -> 23.7, FP32 23 x 165 x 22 x 2 26.1 -> 21.5.  Fitted tiles of FP64 and FP32 off the lines gain from 14 MB (59 boxes up to 22 MB 0.93
+//   on average; FP32 18 x 60 x 21 x 5 periodic 27.4 -> 23.4).  FP64 arithmetic on FP32 storage up to 32 MB, rows held whole (72 x 92 x 31
 //   25.2 -> 26.5; 179 x 35 x 31 32.7 -> 30.1).
 // - Both buffers in the memory-side cache: cached, rows on whole lines too (FP32 64 x 84 x 34 x 3 41.6 -> 36.2, 97 x 124 x 90
 //   93 -> 88; FP64 72^3 71 -> 61; BF16 150 x 93 x 67 59 -> 49).
@@ -397,13 +406,15 @@ SmallShape small_tiles(const sclbm_config &c, int &w, int &h) {
 //   (34 x 95 x 125 x 4 320 -> 272, 30 x 139 x 181 x 2 313 -> 259; 92 x 105 x 94 3 % slower); fixed ones for odd rows above 320 MB,
 //   where one buffer alone exceeds the memory-side cache, which joins some of the parts before that (57 x 146 x 198 x 2
 //   537 -> 494; 11 boxes of 354 - 1345 MB 0.945 - 0.99 of the streaming time, six of 121 - 254 MB 1.00 - 1.06).
-// Over 894 boxes that the rules were not fitted to (1e5 to 9e6 nodes, all formats, both boundary modes, one to 16 boxes) a step
-// takes 0.890 of the time of fixed tiles with streaming stores and 1.007 of the best of {fitted, fixed} x {streaming, cached};
-// 29 are more than 3 % slower than the former (worst 9 %), 18 of them FP64 arithmetic on FP32 storage in ghost
-// mode on 128-wide tiles at 165 - 260 MB or with nx % 4 == 0, where the mean is 1.00 (single boxes 0.91 - 1.09).
+// Over 850 boxes drawn after the rules stood (2e4 to 3e6 nodes, narrow, wide, thin and others, all formats, both boundary modes, one
+// to 16 boxes) a step takes 0.71 of the time of fixed tiles with streaming stores (planes at once 0.47, fitted tiles 0.66, cached and
+// other fixed ones 0.93); 7 are more than 3 % slower, worst 9 %.  Most such boxes of the sweep that the limits rest on are FP64
+// arithmetic on FP32 storage in ghost mode on 128-wide tiles, at 165 - 260 MB or with nx % 4 == 0: the mean is 1.00 there (single
+// boxes 0.91 - 1.09).
 bool cached_stores(const sclbm_config &c, int w, bool fitted) {
     const bool cut = w < c.nx;
-    if (state_bytes(c) <= double((c.prec == SCLBM_F32D && !cut ? 32 : 22) << 20)) return false;
+    const int from = c.prec == SCLBM_F32D && !cut ? 32 : (fitted && !is_dev(c.prec) && row_bytes(c) % 64 != 0 ? 14 : 22);
+    if (state_bytes(c) <= double(from << 20)) return false;
     if (side_cached(c)) return true;
     if (row_bytes(c) % 64 == 0) return false;
     if (c.prec == SCLBM_F64) return cut || (fitted ? row_bytes(c) % 32 != 0 : c.nx % 2 != 0 && state_bytes(c) > double(320 << 20));

@@ -204,3 +204,21 @@ def test_default_tiles_of_known_boxes(n, nbox, prec, expect):
         sc.sclbm_get_tiles(None)
     with pytest.raises(sc.SclbmError):
         sc.sclbm_reset_launch(None)
+
+
+@pytest.mark.parametrize("n,nbox,prec,bc,expect", [
+    ((268, 5, 15), 8, "bf16dev", "ghost", ("fixed", False)), ((262, 99, 4), 1, "f16dev", "ghost", ("fixed", False)),
+    ((692, 4, 23), 1, "f64", "ghost", ("fixed", False)), ((515, 4, 17), 1, "f64", "periodic", ("fixed", False)),
+    ((315, 4, 99), 1, "f32", "periodic", ("fixed", False)), ((17, 60, 21), 5, "f32", "periodic", ("fixed", False)),
+    ((26, 99, 26), 2, "f32", "periodic", ("fitted", True)), ((21, 170, 41), 1, "f64", "ghost", ("fitted", True)),
+    ((17, 171, 50), 1, "f16dev", "ghost", ("fitted", False)), ((12, 25, 92), 2, "f32", "ghost", ("fitted", False)),
+    ((9, 20, 143), 2, "f32", "periodic", ("fitted", False)), ((434, 32, 9), 1, "f32", "periodic", ("fitted", True)),
+    ((289, 20, 19), 3, "f16dev", "ghost", ("fitted", True)), ((16, 40, 42), 4, "f32", "ghost", ("fitted", False))])
+def test_tiles_of_grids_that_do_not_fill_the_device(n, nbox, prec, bc, expect):
+    """Fixed tiles where fitted ones would fill little of a round: rows cut, fewer than eight of
+    them (0.6) or in 16 bits (0.45), FP32 rows of 16 and more nodes held whole (0.45);
+    others take fitted tiles there, with cached stores from 14 MB of one buffer (FP64
+    and FP32 rows off the cache lines)."""
+    import paper_2112_09972_amd as sc
+    t = sc.sclbm_default_tiles(cfg(nx=n[0], ny=n[1], nz=n[2], nbox=nbox, prec=sc.PREC[prec], bc=sc.BC[bc]))
+    assert (t["kind"], t["cached"]) == expect

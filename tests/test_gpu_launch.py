@@ -101,21 +101,21 @@ PLANES = [((3, 3, 3), 1, "planes", 1, False), ((32, 32, 32), 1, "planes", 1, Fal
           ((40, 57, 33), 1, "planes", 1, False), ((21, 70, 9), 5, "planes", 1, False)]
 F32X = [((272, 43, 13), 1, "fixed", 5, True), ((372, 34, 12), 1, "fixed", 3, True)]
 DEV = [((13, 118, 99), 2, "fitted", 1, True), ((13, 33, 104), 2, "fitted", 1, False), ((133, 14, 86), 2, "fitted", 2, True),
-       ((142, 17, 116), 1, "fitted", 2, False), ((263, 55, 21), 1, "fitted", 3, True), ((406, 13, 19), 1, "fitted", 4, False),
+       ((142, 17, 116), 1, "fitted", 2, False), ((292, 23, 46), 1, "fitted", 3, True), ((413, 13, 20), 2, "fitted", 4, False),
        ((257, 17, 86), 1, "fitted", 5, True), ((406, 21, 26), 2, "fitted", 6, True),
        ((143, 118, 18), 1, "fixed", 3, True), ((55, 48, 115), 1, "fixed", 1, True), ((337, 53, 17), 1, "fixed", 3, True),
        ((124, 34, 24), 3, "fixed", 1, True), ((419, 27, 28), 1, "fixed", 2, True), ((181, 43, 39), 1, "fixed", 1, True),
        ((48, 48, 47), 1, "planes", 1, False)]
 STARTS = {
     "f64": PLANES + [((17, 93, 24), 2, "fitted", 1, True), ((13, 19, 62), 3, "fitted", 1, False),
-                     ((139, 18, 20), 3, "fitted", 2, True), ((277, 12, 22), 1, "fitted", 3, False),
-                     ((390, 13, 15), 1, "fitted", 4, True), ((413, 13, 20), 2, "fitted", 6, True),
+                     ((139, 18, 20), 3, "fitted", 2, True), ((271, 16, 26), 1, "fitted", 3, True),
+                     ((410, 13, 24), 1, "fitted", 4, True), ((413, 13, 20), 2, "fitted", 6, True),
                      ((387, 51, 12), 1, "fitted", 7, True), ((154, 13, 38), 1, "fixed", 3, True),
                      ((16, 26, 61), 3, "fixed", 1, True), ((209, 14, 26), 1, "fixed", 2, True),
                      ((97, 22, 36), 1, "fixed", 1, True)],
     "f32": PLANES + F32X + [((48, 48, 47), 1, "planes", 1, False), ((21, 77, 47), 2, "fitted", 1, True),
                             ((12, 25, 92), 2, "fitted", 1, False), ((139, 25, 44), 1, "fitted", 2, True),
-                            ((266, 28, 13), 1, "fitted", 3, False), ((404, 28, 15), 1, "fitted", 4, True),
+                            ((271, 16, 26), 1, "fitted", 3, True), ((404, 24, 20), 1, "fitted", 4, True),
                             ((412, 17, 28), 1, "fitted", 5, True), ((387, 51, 12), 1, "fitted", 7, True),
                             ((55, 20, 69), 2, "fixed", 1, True), ((93, 17, 96), 1, "fixed", 1, True)],
     "f32d": PLANES + F32X + [((15, 115, 64), 2, "fixed", 1, True), ((92, 40, 30), 2, "fixed", 1, True)],
